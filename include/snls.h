@@ -127,7 +127,10 @@ typedef struct {
  *             15; stride1 <= 1; any stride0) and the single-pixel path with
  *             k > 32 (ps = 1, stride1 = 1, ws <= 15, inner product) score
  *             every candidate into it (4 bytes per query row and candidate,
- *             rows padded to 32 candidates) before selecting; squared L2
+ *             rows padded to 32 candidates) before selecting, and with 8 or
+ *             more channels per head also holds copies of q and k split for
+ *             the matrix cores (each 4 bytes per element, channels per head
+ *             padded to 32 or a multiple of 64); squared L2
  *             adds the key-norm term of every candidate, the query norm of
  *             every row, five key pair products per key pixel, frame and
  *             head, the squared norm of every query pixel per frame and head

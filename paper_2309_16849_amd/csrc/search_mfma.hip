@@ -1,0 +1,896 @@
+// search_mfma.hip -- scores of every candidate on the matrix cores for the
+// tiled search route (Sec. 3.2; inner products, any S_Q, S_K <= 1, P <= 7).
+//
+// Same decomposition as search_tile.hip: a candidate's bilinear score is a
+// 4-tap combination of box sums B_D(j) = sum_p c_D(j + p) of the pixel
+// correlations c_D(x) = <q(x), K(x + D)>, D over the union of the integer
+// shifts that the tile's windows read.  Here the contraction over the head's
+// channels runs on the matrix cores.
+//
+// Precision.  A fp32 value x, scaled by a power of two so that its image's
+// largest magnitude lies in [2^14, 2^15), is split into two fp16 numbers, hi
+// = fp16(x) and lo = fp16(x - hi): 22 to 24 significant
+// bits.  All four partial products are formed (v_mfma_f32_16x16x32_f16, fp32
+// accumulation), so the only error beyond the accumulation's is the rounding
+// of lo, unbiased; dropping lo * lo (three products) biases the scores of
+// near-copies and was measured worse (64x64 noise, 16 channels: relative
+// error 7.0e-8 against 4.9e-8).  With the 4-tap pass in 64 bits (one rounding)
+// the scores' error against 64-bit sums is below that of the fp32 vector-unit
+// kernel on every shape measured.
+//
+// Work split (one workgroup of 12 waves = one query tile of one (b, head, t),
+// looping over the frames of the window):
+//  * the tile's halo of q -- hr rows of 16 pixels, tile rows (16 - P) / S_Q + 1
+//    queries wide -- sits in LDS in split form for all frames;
+//  * a wave owns one or two consecutive shift rows D_h.  It streams the key
+//    rows straight from memory into registers (matrix operand B: 16 key
+//    columns x the channels, 2 or 3 column blocks), one key row at a time;
+//    key row Y pairs with halo row y = Y - D_h for each of its shift rows,
+//    so one load serves them all, and the next row's load is in flight while
+//    the current one's sums are formed.  No workgroup barrier inside a frame;
+//  * the 16 x 48 products (x, X) of a (halo row, shift row) go through the
+//    wave's own LDS block, whose diagonals X - x = D_w the lanes read back:
+//    lane = (shift column, part of the tile's columns; 3 parts of 21 lanes
+//    for unions up to 21 shift columns, else 2 of 32).  The horizontal box
+//    sums are formed in registers, the vertical ones as a running tree over
+//    the halo rows (each row adds once: v, v + v', ... as in search_tile.hip),
+//    and every finished box sum goes to its query's window table in LDS;
+//  * the 4-tap pass writes the scores of the frame to the workspace rows.
+//
+// Measured (480x854, T = 5, 64 channels, P = 7, Ws = 9): 11.8 ms with the
+// split copies (0.4 ms) against 20.3 ms on the vector units, whose products
+// alone are 60% of its instructions.  A tile-frame takes about 80,000 cycles:
+// 53,000 streaming (per step and wave of two shift rows: 1,060 for the
+// products -- 614 of them matrix-core time --, 1,380 for the sums, 450 loop
+// and operand issue), 12,000 waiting for the wave with one row more, 9,400 in
+// the 4-tap pass, the rest set-up.  The matrix cores are busy a fifth of the
+// time: the chain product -> LDS -> sums bounds it, at 2 or 3 waves per SIMD.
+// The operand's layout matters: with a pixel's pieces contiguous (16 lanes of
+// a load on 16 cache lines) the same kernel took 20.9 ms.
+#include <math.h>
+#include <type_traits>
+
+#include "snls_internal.h"
+
+namespace snls {
+
+namespace mf {
+// Waves per workgroup and shift rows per wave: 12 waves (3 per SIMD, 168
+// VGPRs each) of up to 2 rows for records of one chunk; 8 (2 per SIMD, 256
+// VGPRs) of up to 3 rows where two chunks' operands are held (480x854, 64
+// channels, P = 7: 12.4 ms, with 12 waves 13.0 and more; 128x128, 32
+// channels: 12 waves 1.29 ms a step, 8 waves 1.37).
+constexpr int waves(int CG) { return CG == 1 ? 12 : 8; }
+constexpr int rows_per_wave(int CG) { return CG == 1 ? 2 : 3; }
+constexpr int HC = 16;           // halo columns = rows of operand A
+constexpr int UW3 = 21;          // shift columns with three column parts (one per lane of a part)
+constexpr int UW2 = 32;          // ... with two: the widest union (16 + 32 - 1 <= 48 key columns)
+constexpr int DP = 52;           // pitch of a product row in LDS (4 DP = 16 mod 64: the writes' banks)
+constexpr int DBUF = HC * DP;    // floats per wave
+constexpr int LDS_BYTES = 160 * 1024;
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+}  // namespace mf
+
+// Geometry of the split copies and of the tiles.
+struct MfGeo {
+  int nc32;     // 32-channel chunks of a pixel record (hi 64 bytes, lo 64 bytes each)
+  int rec;      // bytes of a pixel record
+  int tqh, tqw; // queries per tile
+  int hr;       // halo rows
+  int tiles_x, tiles_y;
+  int qpitch;   // bytes of a pixel record in LDS
+  int o_qs, o_d, o_tab, o_qi, o_ql, o_fl, o_dump, o_uni;  // LDS offsets (bytes)
+  int wp, win;  // window table pitch and size of a query
+};
+
+// Channels of a split record: 32, or a multiple of 64.
+static int mf_chunks(const Geo& g) { return g.Ch <= 32 ? 1 : 2 * ((g.Ch + 63) / 64); }
+
+// ---- split copies ----
+//
+// Scales.  One power of two for a whole image (b, t, head) brings its largest
+// magnitude into [2^14, 2^15), provided that no pixel's largest channel lies
+// below 2^-12 of that (pixels of zeros aside): fp16 subnormals then still hold
+// every pixel to 2^-27 of its largest channel.  An image with a wider range
+// gets a scale per pixel, and its products are scaled pixel by pixel.
+//
+// The statistics of an image come from up to kStatBlocks workgroups, each
+// writing the largest and the smallest non-zero of its pixels' largest
+// magnitudes; every later workgroup reduces them for itself.
+constexpr int kStatBlocks = 256;
+
+// One thread per pixel, its channels' loads in flight together (480x854, 64
+// channels: 0.69 ms with 64 workgroups an image and 4 threads a pixel).
+SNLS_DEV float mf_pixel_max(const float* __restrict__ src, const Geo& g, long long p) {
+  float m = 0.f;
+  int c = 0;
+  for (; c + 8 <= g.Ch; c += 8) {
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = src[(long long)(c + i) * g.HW + p];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(v[i]));
+  }
+  for (; c < g.Ch; ++c) m = fmaxf(m, fabsf(src[(long long)c * g.HW + p]));
+  return m;
+}
+
+__global__ void __launch_bounds__(256) mf_stats_kernel(const float* __restrict__ x, Geo g, float2* __restrict__ stats) {
+  __shared__ float2 part[4];
+  const long long slab = blockIdx.y;  // (b*T + t)*HD + hd
+  const int hd = (int)(slab % g.HD);
+  const float* src = x + ((slab / g.HD) * g.C + (long long)hd * g.Ch) * g.HW;
+  float hi = 0.f, lo = INFINITY;
+  for (long long p = (long long)blockIdx.x * 256 + threadIdx.x; p < g.HW; p += (long long)gridDim.x * 256) {
+    const float m = mf_pixel_max(src, g, p);
+    hi = fmaxf(hi, m);
+    if (m > 0.f) lo = fminf(lo, m);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    hi = fmaxf(hi, __shfl_xor(hi, off));
+    lo = fminf(lo, __shfl_xor(lo, off));
+  }
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = make_float2(hi, lo);
+  __syncthreads();
+  if (threadIdx.x == 0)
+    stats[slab * kStatBlocks + blockIdx.x] =
+        make_float2(fmaxf(fmaxf(part[0].x, part[1].x), fmaxf(part[2].x, part[3].x)),
+                    fminf(fminf(part[0].y, part[1].y), fminf(part[2].y, part[3].y)));
+}
+
+// Power-of-two factors for a largest magnitude m: up brings it into [2^14,
+// 2^15) (for 2^-112 and above), down takes it back.
+SNLS_DEV void mf_factors(float m, float* up, float* down) {
+  int e = (int)((__float_as_uint(m) >> 23) & 255u) - 127;
+  e = min(max(e, -112), 127);
+  if (m == 0.f) e = 14;
+  *up = __uint_as_float((unsigned)(127 + 14 - e) << 23);
+  // 2^(e - 14) by two factors, neither of them denormal
+  const int e1 = max(e, -100);
+  *down = __uint_as_float((unsigned)(127 + e1) << 23) * __uint_as_float((unsigned)(127 + (e - e1) - 14) << 23);
+}
+
+// One workgroup = 64 pixels of one (b, t, head): channels x pixels through
+// LDS, 64 channels at a time, then 8 channels per thread are scaled, split
+// and written as two 16-byte pieces.  info: the image's scale, or 0 when
+// its pixels have their own (in scale).
+__global__ void __launch_bounds__(256) mf_split_kernel(const float* __restrict__ x, Geo g, int nc32,
+                                                       const float2* __restrict__ stats, int nstat,
+                                                       unsigned char* __restrict__ xs, float* __restrict__ scale,
+                                                       float* __restrict__ info) {
+  using namespace mf;
+  __shared__ float tile[64][65];
+  const long long slab = blockIdx.y;  // (b*T + t)*HD + hd
+  const int hd = (int)(slab % g.HD);
+  const long long p0 = (long long)blockIdx.x * 64;
+  const float* src = x + ((slab / g.HD) * g.C + (long long)hd * g.Ch) * g.HW;
+  const int px = threadIdx.x & 63, qt = threadIdx.x >> 6;
+  const bool pin = p0 + px < g.HW;
+  const int rec = nc32 * 128;
+  // row y of the plane: 16-byte pieces (8 channels, hi or lo) of its pixels,
+  // piece after piece: [32-channel chunk][hi, lo][4 pieces][W]
+  const int p = (int)p0 + px;
+  const int y = p / g.W;
+  unsigned char* dst = xs + slab * g.HW * rec + ((long long)y * g.W * rec + (long long)(p - y * g.W) * 16);
+  const long long pst = (long long)g.W * 16;  // bytes from piece to piece
+  const int nch = nc32 * 32;                  // channels with padding
+  float hi = 0.f, lo = INFINITY;
+  for (int i = px; i < nstat; i += 64) {
+    const float2 st = stats[slab * kStatBlocks + i];
+    hi = fmaxf(hi, st.x);
+    lo = fminf(lo, st.y);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    hi = fmaxf(hi, __shfl_xor(hi, off));
+    lo = fminf(lo, __shfl_xor(lo, off));
+  }
+  const bool one = !(lo < hi * 0x1p-12f);  // the same for every workgroup of the image
+  float up, down;
+  if (one) {
+    mf_factors(hi, &up, &down);
+  } else {
+    mf_factors(pin ? mf_pixel_max(src, g, p0 + px) : 0.f, &up, &down);  // (the same for the four threads of a pixel)
+    if (qt == 0 && pin) scale[slab * g.HW + p0 + px] = down;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) info[slab] = one ? down : 0.f;
+  for (int c0 = 0; c0 < nch; c0 += 64) {
+    if (c0) __syncthreads();
+    for (int i = qt; i < 64; i += 4) {
+      const int c = c0 + i;
+      tile[i][px] = (c < g.Ch && pin) ? src[(long long)c * g.HW + p0 + px] : 0.f;
+    }
+    __syncthreads();
+    // piece pc (channels 8 pc ..) of pixel px: consecutive threads write
+    // consecutive 16 bytes
+    for (int pc = qt; pc < min(nch - c0, 64) / 8; pc += 4) {
+      if (!pin) continue;
+      half8 h8, l8;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float v = tile[8 * pc + i][px] * up;
+        const _Float16 h = (_Float16)v;
+        const float r = v - (float)h;
+        h8[i] = h;
+        l8[i] = (_Float16)(r == r ? r : 0.f);  // an infinity keeps its sign in hi
+      }
+      unsigned char* o = dst + ((c0 / 32 + pc / 4) * 8 + (pc & 3)) * pst;
+      *reinterpret_cast<half8*>(o) = h8;
+      *reinterpret_cast<half8*>(o + 4 * pst) = l8;
+    }
+  }
+}
+
+// Box sums of width P of L values in registers (N = L - P + 1 results), the
+// same tree as search_tile.hip's: 4 a + 2 b + c.
+template <int P, int N>
+SNLS_DEV void mf_box(const float (&v)[N + P - 1], float (&o)[N]) {
+  constexpr int L = N + P - 1;
+  if constexpr (P == 1) {
+#pragma unroll
+    for (int x = 0; x < N; ++x) o[x] = v[x];
+  } else {
+    float b2[L - 1];
+#pragma unroll
+    for (int x = 0; x < L - 1; ++x) b2[x] = v[x] + v[x + 1];
+    if constexpr ((P & 4) != 0) {
+#pragma unroll
+      for (int x = 0; x < N; ++x) {
+        float r = b2[x] + b2[x + 2];
+        if constexpr ((P & 2) != 0) r += b2[x + 4];
+        if constexpr ((P & 1) != 0) r += v[x + P - 1];
+        o[x] = r;
+      }
+    } else {
+#pragma unroll
+      for (int x = 0; x < N; ++x) {
+        float r = b2[x];
+        if constexpr ((P & 1) != 0) r += v[x + P - 1];
+        o[x] = r;
+      }
+    }
+  }
+}
+
+// Running vertical box sum: push the value of row y, get the sum of rows
+// y-P+1 .. y (meaningful from the P-th push on).  State: the last value, the
+// last pair sums and quad sums that later results read.  PH = y mod 3: the
+// quad sums of P = 7 sit in a ring of three, so they need not be moved.
+template <int P>
+struct RunBox {
+  float v1;        // v(y-1)
+  float b2a, b2b;  // b2(y-2), b2(y-3)  (b2(i) = v(i) + v(i+1))
+  float b4[3];     // quad sums b4(i) = b2(i) + b2(i+2): P = 7: b4(y-4 .. y-6); P = 5, 6: b4[0] = b4(y-4), b4[1] = b4(y-5)
+  SNLS_DEV void clear() { v1 = b2a = b2b = b4[0] = b4[1] = b4[2] = 0.f; }
+  template <int PH>
+  SNLS_DEV float push(float v) {
+    if constexpr (P == 1) {
+      return v;
+    } else {
+      const float b2 = v1 + v;  // b2(y-1)
+      float r;
+      if constexpr (P == 2) {
+        r = b2;
+      } else if constexpr (P == 3) {
+        r = b2a + v;  // b2(y-2) + v(y)
+        b2a = b2;
+      } else {
+        const float q4 = b2b + b2;  // b4(y-3)
+        if constexpr (P == 4) r = q4;
+        if constexpr (P == 5) {
+          r = b4[0] + v;  // b4(y-4) + v(y)
+          b4[0] = q4;
+        }
+        if constexpr (P == 6) {
+          r = b4[1] + b2;  // b4(y-5) + b2(y-1)
+          b4[1] = b4[0];
+          b4[0] = q4;
+        }
+        if constexpr (P == 7) {
+          r = b4[PH] + b2a + v;  // b4(y-6) + b2(y-2) + v(y)
+          b4[PH] = q4;
+        }
+        b2b = b2a;
+        b2a = b2;
+      }
+      v1 = v;
+      return r;
+    }
+  }
+};
+
+// What the waves of a workgroup need of one frame step (uniform values).
+struct MfFrame {
+  const unsigned char* kplane;  // split key plane of the frame, its scales
+  const float* kscale;
+  int W, rec, plane_bytes;      // frame width; bytes of a pixel record and of a plane
+  int row0;                     // frame row of (halo row 0, the wave's first shift row)
+  int H, hr, ngrp, qpitch;
+  int dr0, col0;                // wave's first shift row less the union's, frame column of product column 0
+  int s0, tqw, wp;
+  float kuni, quni;             // scale of the key and query images (0: per pixel, in kscale and qsc)
+};
+
+// The box sums of ND consecutive shift rows for the whole tile, NB blocks of
+// 16 key columns, NPART column parts (see the head of the file).  Step s
+// reads key row s + row0 and pairs it with halo rows s, s - 1, ...; halo rows
+// outside [0, hr) (the first and last ND - 1 steps) are computed from a
+// clamped row: they enter only sums that are never written, and the loop has
+// no branches.
+template <int PS, int CG, bool S1, int ND, int NB, int NPART, bool ONE>
+SNLS_DEV void mf_stream(const MfFrame& f, const unsigned char* qlds, const float* qsc, float* dbuf, const int2* qi,
+                        float* tab, float* dump0) {
+  using namespace mf;
+  constexpr int NX = HC - PS + 1;                // patch origins per halo row
+  constexpr int NXP = (NX + NPART - 1) / NPART;  // ... of a part (neighbouring parts may share some)
+  constexpr int NV = NXP + PS - 1;               // products a lane reads per row
+  constexpr int LW = NPART == 3 ? UW3 : UW2;     // lanes of a part
+  constexpr unsigned OOB = 0x80000000u;
+  const int lane = threadIdx.x & 63;
+  const int lj = lane & 15, lg = lane >> 4;
+  const int part = min(lane / LW, NPART - 1);
+  const int le = lane - part * LW;               // shift column (lane 63 of three parts: column 21, never read)
+  const int xh = min(part * NXP, NX - NXP);      // first patch origin of this part
+  const __amdgpu_buffer_rsrc_t k_rs =
+      __builtin_amdgcn_make_buffer_rsrc((void*)f.kplane, (short)0, f.plane_bytes, 0x00020000);
+  unsigned voff[NB];  // byte offsets of this lane's key columns (outside the frame: reads 0)
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    const int gx = f.col0 + 16 * n + lj;
+    const bool in = gx >= 0 && gx < f.W;
+    voff[n] = in ? (unsigned)((lg * f.W + gx) * 16) : OOB;
+  }
+  half8 bh[NB][CG], bl[NB][CG];
+  // operand A of step s, channel group gi; rows outside the frame read 0
+  // (a scalar offset of the whole plane puts every lane past its end)
+  auto load_k = [&](int s, int gi) {
+    const int gy = f.row0 + s;
+    const bool in = gy >= 0 && gy < f.H;
+    const int part4 = f.W * 64;  // bytes of the hi (or lo) pieces of a chunk
+    const int so = in ? gy * f.W * f.rec + gi * CG * 2 * part4 : f.plane_bytes;
+#pragma unroll
+    for (int c = 0; c < CG; ++c)
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        const int sc = in ? so + c * 2 * part4 : so;
+        bh[n][c] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(k_rs, voff[n], sc, 0));
+        bl[n][c] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(k_rs, voff[n], in ? sc + part4 : so, 0));
+      }
+  };
+  RunBox<PS> st[ND][NXP];
+#pragma unroll
+  for (int i = 0; i < ND; ++i)
+#pragma unroll
+    for (int x = 0; x < NXP; ++x) st[i][x].clear();
+  float* const dw = dbuf + lj * DP + 4 * lg;             // this lane's products
+  const float* const dr = dbuf + xh * (DP + 1) + le;     // ... and its diagonal
+  float* const dump = dump0 + lane;                      // box sums that no query reads go here
+  // strided queries: query column of each patch origin (0 where it is none, bit x of xok clear)
+  int jx[NXP];
+  unsigned xok = 0;
+#pragma unroll
+  for (int x = 0; x < NXP; ++x) {
+    const int j = (xh + x) / f.s0;
+    const bool ok = j * f.s0 == xh + x;
+    jx[x] = ok ? j : 0;
+    xok |= (ok ? 1u : 0u) << x;
+  }
+  // images with a scale per pixel: the products of key row s and halo row y scaled back
+  auto scale_products = [&](f32x4(&a)[NB], int s, int y) {
+    const __amdgpu_buffer_rsrc_t s_rs =
+        __builtin_amdgcn_make_buffer_rsrc((void*)f.kscale, (short)0, f.plane_bytes / f.rec * 4, 0x00020000);
+    const float eq = f.quni != 0.f ? f.quni : qsc[min(max(y, 0), f.hr - 1) * HC + lj];
+    const int gy = f.row0 + s;
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int gx = f.col0 + 16 * n + 4 * lg + u;
+        const bool in = gy >= 0 && gy < f.H && gx >= 0 && gx < f.W;
+        const unsigned off = in && f.kuni == 0.f ? (unsigned)((gy * f.W + gx) * 4) : OOB;
+        const float ek = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(s_rs, off, 0, 0));
+        a[n][u] = a[n][u] * (f.kuni != 0.f ? f.kuni : ek) * eq;
+      }
+  };
+  const unsigned char* const ap0 = qlds + lj * f.qpitch + lg * 16;
+  const int qrow = HC * f.qpitch;
+  const int nstep = f.hr + ND - 1;
+  load_k(0, 0);
+  auto step = [&](int s, auto phase) {
+    constexpr int PH = decltype(phase)::value;
+    f32x4 acc[ND][NB];
+#pragma unroll
+    for (int i = 0; i < ND; ++i)
+#pragma unroll
+      for (int n = 0; n < NB; ++n) acc[i][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto products = [&](int gi) {
+#pragma unroll
+      for (int i = 0; i < ND; ++i) {
+        const unsigned char* ap = ap0 + min(max(s - i, 0), f.hr - 1) * qrow + gi * (CG * 128);
+        half8 ah[CG], al[CG];  // operand B
+#pragma unroll
+        for (int c = 0; c < CG; ++c) {
+          ah[c] = *reinterpret_cast<const half8*>(ap + c * 128);
+          al[c] = *reinterpret_cast<const half8*>(ap + c * 128 + 64);
+        }
+        // the small products of all chunks first: their roundings are small too
+        auto mul = [&](const half8(&kk)[NB][CG], const half8(&qq)[CG], int c) {
+#pragma unroll
+          for (int n = 0; n < NB; ++n)
+            acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kk[n][c], qq[c], acc[i][n], 0, 0, 0);
+        };
+#pragma unroll
+        for (int c = 0; c < CG; ++c) mul(bl, al, c);
+#pragma unroll
+        for (int c = 0; c < CG; ++c) {
+          mul(bh, al, c);
+          mul(bl, ah, c);
+        }
+#pragma unroll
+        for (int c = 0; c < CG; ++c) mul(bh, ah, c);
+      }
+    };
+    for (int gi = 0; gi + 1 < f.ngrp; ++gi) {
+      products(gi);
+      load_k(s, gi + 1);
+    }
+    products(f.ngrp - 1);
+    load_k(s + 1, 0);  // in flight during the sums below
+    // The products of shift row i + 1 enter the wave's LDS block right behind
+    // row i's reads (a wave's LDS accesses complete in order), so that they
+    // are there when row i's sums are done.
+    auto put_products = [&](int i) {
+      // row x = lj, columns X = 16 n + 4 lg ..
+      if constexpr (!ONE) scale_products(acc[i], s, s - i);
+#pragma unroll
+      for (int n = 0; n < NB; ++n) *reinterpret_cast<f32x4*>(dw + 16 * n) = acc[i][n];
+      wave_lds_sync();
+    };
+    put_products(0);
+#pragma unroll
+    for (int i = 0; i < ND; ++i) {
+      float v[NV];
+#pragma unroll
+      for (int x = 0; x < NV; ++x) v[x] = dr[x * (DP + 1)];
+      wave_lds_sync();
+      const int yq = s - i - (PS - 1);  // patch origin row of the sums this step finishes
+      const bool live = yq >= 0 && yq <= f.hr - PS && (S1 || yq % f.s0 == 0);
+      // the queries of that row: first shifts and table base (any row when
+      // there is none: nothing is written then)
+      const int jr = live ? (S1 ? yq : yq / f.s0) * f.tqw : 0;
+      int2 w[NXP];
+#pragma unroll
+      for (int x = 0; x < NXP; ++x) w[x] = qi[jr + (S1 ? xh + x : jx[x])];
+      if (i + 1 < ND) put_products(i + 1);
+      float hb[NXP];
+      mf_box<PS, NXP>(v, hb);
+#pragma unroll
+      for (int x = 0; x < NXP; ++x) hb[x] = st[i][x].template push<PH>(hb[x]);
+      // the finished box sums to their queries' tables: entry (shift row less
+      // the query's first, the same for columns) where it lies in the table
+      if (live) {
+        const int cell = (f.dr0 + i) * f.wp + le;
+#pragma unroll
+        for (int x = 0; x < NXP; ++x) {
+          const unsigned u = (unsigned)(f.dr0 + i - (w[x].x >> 16)), c = (unsigned)(le - (int)(short)w[x].x);
+          bool ok = max(u, c) < (unsigned)f.wp;
+          if (!S1) ok = ok && ((xok >> x) & 1);
+          float* const at = ok ? tab + (w[x].y + cell) : dump;
+          *at = hb[x];
+        }
+      }
+    }
+  };
+  if constexpr (PS == 7) {
+    for (int s = 0; s < nstep; s += 3) {
+      step(s, std::integral_constant<int, 0>{});
+      if (s + 1 >= nstep) break;
+      step(s + 1, std::integral_constant<int, 1>{});
+      if (s + 2 >= nstep) break;
+      step(s + 2, std::integral_constant<int, 2>{});
+    }
+  } else {
+    for (int s = 0; s < nstep; ++s) step(s, std::integral_constant<int, 0>{});
+  }
+}
+
+// CG: 32-channel chunks of a record multiplied per load (1 or 2).  S1: query stride 1.
+template <int PS, int CG, bool S1>
+__global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_mfma_scores_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const unsigned char* __restrict__ qs,
+    const float* __restrict__ qscale, const float* __restrict__ qinfo, const unsigned char* __restrict__ ks,
+    const float* __restrict__ kscale, const float* __restrict__ kinfo, const float* __restrict__ flows, Geo g, MfGeo mg, float* __restrict__ scores, int pitch) {
+  using namespace mf;
+  constexpr int LO = -(PS / 2);
+  constexpr int NW = waves(CG), NT = NW * 64, NDW = rows_per_wave(CG);
+  __shared__ __attribute__((aligned(16))) unsigned char smem[LDS_BYTES];
+  unsigned char* const qlds = smem;
+  float* const qsc = reinterpret_cast<float*>(smem + mg.o_qs);
+  float* const tab = reinterpret_cast<float*>(smem + mg.o_tab);
+  float2* const fl = reinterpret_cast<float2*>(smem + mg.o_fl);  // offsets: [frame of the window][query]
+  // two buffers (this frame's and the next one's):
+  // a query's first shift row (high half) and column less the union's, table base less their entry
+  int2* const qi = reinterpret_cast<int2*>(smem + mg.o_qi);
+  int2* const ql = reinterpret_cast<int2*>(smem + mg.o_ql);  // a query's first shift row and column
+  float* const dump = reinterpret_cast<float*>(smem + mg.o_dump);
+  int* const uni = reinterpret_cast<int*>(smem + mg.o_uni);  // min N_h, max N_h, min N_w, max N_w of each frame
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  float* const dbuf = reinterpret_cast<float*>(smem + mg.o_d) + wave * DBUF;
+
+  // XCD-aware order: each XCD takes a contiguous run of tiles; the query
+  // frames, heads and batch entries of one tile are consecutive workgroups
+  // (they share key frames in the XCD's L2).
+  const long long nwg = (long long)gridDim.x;
+  const long long xcd = blockIdx.x % 8, xq = nwg / 8, xrem = nwg % 8;
+  const long long wg = xcd * xq + (xcd < xrem ? xcd : xrem) + blockIdx.x / 8;
+  const int nimg = g.B * g.HD * g.T;
+  const int img = (int)(wg % nimg);
+  const int trem = (int)(wg / nimg);
+  const int ty = trem / mg.tiles_x, tx = trem % mg.tiles_x;
+  const int t = img % g.T;
+  const int hd = (img / g.T) % g.HD;
+  const int b = img / (g.T * g.HD);
+  const int s0 = S1 ? 1 : g.s0, tqh = mg.tqh, tqw = mg.tqw, qn = tqh * tqw, hr = mg.hr;
+  const int my0 = ty * tqh, mx0 = tx * tqw;  // tile origin (query grid)
+  const int y0 = my0 * s0, x0 = mx0 * s0;    // tile origin (pixels)
+  const int Y0 = y0 + LO, X0 = x0 + LO;      // halo origin
+  const int ws = g.ws, r = g.r, wp = mg.wp, win = mg.win, rec = mg.rec;
+  constexpr unsigned OOB = 0x80000000u;  // buffer offset past any extent: reads 0
+  const unsigned plane_bytes = (unsigned)(g.HW * rec);
+  const int dt0 = max(-g.wt, -t), dt1 = min(g.wt, g.T - 1 - t);  // frames inside the clip
+  const int nfr = dt1 - dt0 + 1;
+
+  auto slab = [&](int tt) { return ((long long)b * g.T + tt) * g.HD + hd; };
+
+  // ---- the halo of q (split records and scales), the tile's offsets ----
+  const float quni = qinfo[slab(t)];  // (uniform)
+  if (quni == 0.f)
+    for (int p = tid; p < hr * HC; p += NT) {
+      const int gy = Y0 + p / HC, gx = X0 + p % HC;
+      const bool in = gy >= 0 && gy < g.H && gx >= 0 && gx < g.W;
+      qsc[p] = in ? qscale[slab(t) * g.HW + (long long)gy * g.W + gx] : 0.f;
+    }
+  for (int e = tid; e < nfr * qn; e += NT) {
+    const int fi = e / qn, j = e - fi * qn, dt = dt0 + fi;
+    const int h = y0 + s0 * (j / tqw), w = x0 + s0 * (j % tqw);
+    float2 F = make_float2(0.f, 0.f);
+    if (dt != 0 && h < g.H && w < g.W) {
+      const long long base = (((long long)b * g.T + t) * g.nslot + flow_slot(dt, g.wt)) * 2;
+      const long long pix = (long long)h * g.W + w;
+      F = make_float2(flows[base * g.HW + pix], flows[(base + 1) * g.HW + pix]);
+    }
+    fl[e] = F;
+  }
+  {
+    const __amdgpu_buffer_rsrc_t q_rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(qs + slab(t) * g.HW * rec), (short)0, (int)plane_bytes, 0x00020000);
+    const int npix = hr * HC, n = npix * (rec / 16);
+    for (int e0 = tid; e0 < n; e0 += 4 * NT) {  // four loads in flight
+      u32x4 v[4];
+      int at[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int e = e0 + i * NT;
+        const int pc = e / npix, p = e - pc * npix;
+        const int gy = Y0 + p / HC, gx = X0 + p % HC;
+        const bool in = e < n && gy >= 0 && gy < g.H && gx >= 0 && gx < g.W;
+        at[i] = p * mg.qpitch + pc * 16;
+        v[i] = __builtin_amdgcn_raw_buffer_load_b128(
+            q_rs, in ? (unsigned)(gy * g.W * rec + (pc * g.W + gx) * 16) : OOB, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (e0 + i * NT < n) *reinterpret_cast<u32x4*>(qlds + at[i]) = v[i];
+    }
+  }
+  __syncthreads();
+  // a query's first integer shifts of a frame, and its last ones + 1.
+  // Offsets that are not finite or absurdly large count as zero here; their
+  // candidates fail the exact validity test below.
+  auto lo_of = [&](float F) { return (int)floorf(cand_disp(fabsf(F) < kFarDisp ? F : 0.f, g.s1, 0, r)); };
+  auto hi_of = [&](float F) { return (int)floorf(cand_disp(fabsf(F) < kFarDisp ? F : 0.f, g.s1, ws - 1, r)) + 1; };
+  // unions of the frames' shifts: one wave per frame
+  for (int fi = wave; fi < nfr; fi += NW) {
+    int a0 = INT_MAX, a1 = INT_MIN, a2 = INT_MAX, a3 = INT_MIN;
+    for (int j = lane; j < qn; j += 64) {
+      if (y0 + s0 * (j / tqw) < g.H && x0 + s0 * (j % tqw) < g.W) {
+        const float2 F = fl[fi * qn + j];
+        a0 = min(a0, lo_of(F.x));
+        a1 = max(a1, hi_of(F.x));
+        a2 = min(a2, lo_of(F.y));
+        a3 = max(a3, hi_of(F.y));
+      }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      a0 = min(a0, __shfl_xor(a0, off));
+      a1 = max(a1, __shfl_xor(a1, off));
+      a2 = min(a2, __shfl_xor(a2, off));
+      a3 = max(a3, __shfl_xor(a3, off));
+    }
+    if (lane == 0) {
+      uni[4 * fi] = a0;
+      uni[4 * fi + 1] = a1;
+      uni[4 * fi + 2] = a2;
+      uni[4 * fi + 3] = a3;
+    }
+  }
+  __syncthreads();
+  // the union, clipped to the shifts that a valid cell can read: its centre
+  // lies in the frame, so its taps lie in rows [-h, H - h] of a query at row h
+  const int h_last = min(y0 + (tqh - 1) * s0, (g.nH - 1) * s0);
+  const int w_last = min(x0 + (tqw - 1) * s0, (g.nW - 1) * s0);
+  auto union_of = [&](int fi, int& u0, int& u1, int& u2, int& u3) {
+    u0 = max(__builtin_amdgcn_readfirstlane(uni[4 * fi]), -h_last);
+    u1 = min(__builtin_amdgcn_readfirstlane(uni[4 * fi + 1]), g.H - y0);
+    u2 = max(__builtin_amdgcn_readfirstlane(uni[4 * fi + 2]), -w_last);
+    u3 = min(__builtin_amdgcn_readfirstlane(uni[4 * fi + 3]), g.W - x0);
+  };
+  auto set_queries = [&](int fi) {
+    int u0, u1, u2, u3;
+    union_of(fi, u0, u1, u2, u3);
+    for (int j = tid; j < qn; j += NT) {
+      const float2 F = fl[fi * qn + j];
+      const int lh = lo_of(F.x), lw = lo_of(F.y);
+      // relative to the union; a window that far from it reads none of it
+      const int rh = min(max(lh - u0, -16384), 16383), rw = min(max(lw - u2, -16384), 16383);
+      qi[(fi & 1) * qn + j] = make_int2((rh << 16) | (rw & 0xffff), j * win - rh * wp - rw);
+      ql[(fi & 1) * qn + j] = make_int2(lh, lw);
+    }
+  };
+  set_queries(0);
+  __syncthreads();
+
+  const long long rowb = (((long long)b * g.HD + hd) * g.T + t) * g.nH;
+  for (int fi = 0; fi < nfr; ++fi) {
+    const int dt = dt0 + fi, t2 = t + dt;
+    const int cbase = (dt + g.wt) * ws * ws;
+    int dmin_h, dmax_h, dmin_w, dmax_w;
+    union_of(fi, dmin_h, dmax_h, dmin_w, dmax_w);
+    const int UH = dmax_h - dmin_h + 1, UW = dmax_w - dmin_w + 1;
+    const bool none = UH <= 0 || UW <= 0;  // every cell of the frame is invalid
+    const float2* const ff = fl + fi * qn;
+    const float kuni = kinfo[slab(t2)];
+    // the images' scales, where the sums have not been scaled back yet
+    const float back = kuni != 0.f && quni != 0.f ? kuni * quni : 1.f;
+    if (UW <= UW2) {
+      // shift rows of a round, spread over the waves: up to two each, one
+      // each for unions that need the two-part lane layout and for images
+      // with a scale per pixel.  No barrier
+      // inside a round: a wave without shift rows goes on.
+      const bool one = kuni != 0.f && quni != 0.f;  // both images have one scale
+      const int per = NW * (one && UW <= UW3 ? NDW : 1);
+      for (int rr0 = 0; rr0 < (none ? 0 : UH); rr0 += per) {
+        const int nr = min(per, UH - rr0);
+        const int nd = nr / NW + (wave < nr % NW ? 1 : 0);
+        MfFrame f;
+        f.kplane = ks + slab(t2) * g.HW * rec;
+        f.kscale = kscale + slab(t2) * g.HW;
+        f.W = g.W;
+        f.H = g.H;
+        f.rec = rec;
+        f.plane_bytes = (int)plane_bytes;
+        f.dr0 = rr0 + wave * (nr / NW) + min(wave, nr % NW);
+        f.row0 = Y0 + dmin_h + f.dr0;
+        f.hr = hr;
+        f.ngrp = mg.nc32 / CG;
+        f.qpitch = mg.qpitch;
+        f.col0 = X0 + dmin_w;
+        f.s0 = s0;
+        f.tqw = tqw;
+        f.wp = wp;
+        f.kuni = kuni;
+        f.quni = quni;
+        const int2* const qif = qi + (fi & 1) * qn;
+        if (!one) {
+          if (nd == 1) mf_stream<PS, CG, S1, 1, 3, 2, false>(f, qlds, qsc, dbuf, qif, tab, dump);
+        } else if (UW <= 17) {  // 16 + UW - 1 key columns in two blocks
+          if (nd == 1) mf_stream<PS, CG, S1, 1, 2, 3, true>(f, qlds, qsc, dbuf, qif, tab, dump);
+          else if (nd == 2) mf_stream<PS, CG, S1, 2, 2, 3, true>(f, qlds, qsc, dbuf, qif, tab, dump);
+          else if (nd == 3 && NDW == 3) mf_stream<PS, CG, S1, NDW, 2, 3, true>(f, qlds, qsc, dbuf, qif, tab, dump);
+        } else if (UW <= UW3) {
+          if (nd == 1) mf_stream<PS, CG, S1, 1, 3, 3, true>(f, qlds, qsc, dbuf, qif, tab, dump);
+          else if (nd == 2) mf_stream<PS, CG, S1, 2, 3, 3, true>(f, qlds, qsc, dbuf, qif, tab, dump);
+          else if (nd == 3 && NDW == 3) mf_stream<PS, CG, S1, NDW, 3, 3, true>(f, qlds, qsc, dbuf, qif, tab, dump);
+        } else if (nd == 1) {
+          mf_stream<PS, CG, S1, 1, 3, 2, true>(f, qlds, qsc, dbuf, qif, tab, dump);
+        }
+      }
+      __syncthreads();
+      if (fi + 1 < nfr) set_queries(fi + 1);
+      // ---- 4-tap combination and exact validity: one thread per window
+      // column, so that a store's lanes write runs of ws scores ----
+      for (int e = tid; e < qn * ws; e += NT) {
+        const int j = e / ws, dw = e - j * ws;
+        const int jh = j / tqw;
+        const int mh = my0 + jh, mw = mx0 + j - jh * tqw;
+        if (mh >= g.nH || mw >= g.nW) continue;
+        const int h = mh * s0, w = mw * s0;
+        float* srow = scores + ((rowb + mh) * g.nW + mw) * pitch + cbase + dw;
+        const int2 lo = ql[(fi & 1) * qn + j];
+        const float2 F = ff[j];
+        const float disp_w = cand_disp(F.y, g.s1, dw, r);
+        const bool okw = centre_ok(w, disp_w, g.W);
+        const float fl_w = floorf(disp_w), aw = disp_w - fl_w;
+        // table reads only matter for valid cells (row 0 / column 0 otherwise)
+        const float* const cp = tab + j * win + (okw ? (int)fl_w - lo.y : 0);
+        for (int dh = 0; dh < ws; ++dh) {
+          const float disp_h = cand_disp(F.x, g.s1, dh, r);
+          const bool ok = okw && centre_ok(h, disp_h, g.H);
+          const float fl_h = floorf(disp_h), ah = disp_h - fl_h;
+          const float* const r0p = cp + (ok ? (int)fl_h - lo.x : 0) * wp;
+          // in 64 bits: one rounding per score instead of nine
+          const double t0 = r0p[0], b0 = r0p[wp];
+          const double top = fma((double)aw, (double)r0p[1] - t0, t0);
+          const double bot = fma((double)aw, (double)r0p[wp + 1] - b0, b0);
+          const float dv = (float)fma((double)ah, bot - top, top) * back;
+          srow[dh * ws] = ok && dv == dv ? dv : -INFINITY;  // NaN scores as invalid
+        }
+      }
+    } else {
+      // union too wide for the lanes: this frame's candidates one by one
+      // (inner products for both distances, as the top-k pass expects)
+      Geo gp = g;
+      gp.dist = SNLS_DIST_PROD;
+      if (fi + 1 < nfr) set_queries(fi + 1);
+      for (int e = tid; e < qn * ws; e += NT) {
+        const int j = e / ws, dh = e % ws;
+        const int mh = my0 + j / tqw, mw = mx0 + j % tqw;
+        if (mh >= g.nH || mw >= g.nW) continue;
+        const int h = mh * s0, w = mw * s0;
+        const float2 F = ff[j];
+        const float disp_h = cand_disp(F.x, g.s1, dh, r);
+        const bool okh = centre_ok(h, disp_h, g.H);
+        for (int dw = 0; dw < ws; ++dw) {
+          const float disp_w = cand_disp(F.y, g.s1, dw, r);
+          float d = -INFINITY;
+          if (okh && centre_ok(w, disp_w, g.W)) d = score_candidate(q, k, gp, b, hd, t, h, w, t2, disp_h, disp_w);
+          scores[((rowb + mh) * g.nW + mw) * pitch + cbase + dh * ws + dw] = d;
+        }
+      }
+    }
+    __syncthreads();  // the tables are free, the next frame's queries set
+  }
+}
+
+// Tile geometry for tqh query rows; false when the LDS of one CU cannot hold it.
+static bool mf_geo(const Geo& g, int tqh, MfGeo* m) {
+  m->nc32 = mf_chunks(g);
+  m->rec = m->nc32 * 128;
+  m->tqw = (mf::HC - g.ps) / g.s0 + 1;
+  m->tqh = tqh;
+  m->hr = (tqh - 1) * g.s0 + g.ps;
+  m->tiles_x = (g.nW + m->tqw - 1) / m->tqw;
+  m->tiles_y = (g.nH + tqh - 1) / tqh;
+  m->qpitch = m->rec + 16;  // an odd number of 16-byte slots: consecutive pixels on different banks
+  m->wp = g.ws + 2;
+  m->win = m->wp * m->wp;
+  const long long qn = (long long)m->tqh * m->tqw;
+  long long o = (long long)m->hr * mf::HC * m->qpitch;
+  m->o_qs = (int)o;
+  o += (long long)m->hr * mf::HC * 4;
+  m->o_d = (int)o;
+  o += (long long)mf::waves(m->nc32 > 1 ? 2 : 1) * mf::DBUF * 4;
+  m->o_qi = (int)o;
+  o += 2 * qn * 8;
+  m->o_ql = (int)o;
+  o += 2 * qn * 8;
+  m->o_fl = (int)o;
+  o += (2 * g.wt + 1) * qn * 8;
+  m->o_dump = (int)o;
+  o += 64 * 4;
+  m->o_uni = (int)o;
+  o += (2 * g.wt + 1) * 16;
+  m->o_tab = (int)o;
+  o += qn * m->win * 4;
+  return o <= mf::LDS_BYTES;
+}
+
+// Query rows per tile: the tallest tile has the smallest halo overhead, but
+// the workgroups (one per CU at a time) should fill the 256 CUs evenly: the
+// height with the least (waves of workgroups) x (halo rows + a fixed part).
+static bool mf_tile(const Geo& g, MfGeo* best) {
+  double bc = 0;
+  bool any = false;
+  for (int tqh = 1; tqh <= 16; ++tqh) {
+    MfGeo m;
+    if (!mf_geo(g, tqh, &m) || (tqh > 1 && m.hr > 17)) break;
+    const double nwg = (double)m.tiles_x * m.tiles_y * g.B * g.HD * g.T;
+    const double cost = ceil(nwg / 256.0) * (m.hr + 4);
+    if (!any || cost <= bc) {
+      bc = cost;
+      *best = m;
+      any = true;
+    }
+  }
+  return any;
+}
+
+// Heads of 8 channels or more: fewer would be padded to 32 (the contraction is
+// then mostly zeros; 2 x 4-channel heads keep the vector-unit kernel).
+bool mfma_supported(const Geo& g) {
+  if (!tile_supported(g) || g.Ch < 8) return false;
+  // 32-bit byte offsets inside one frame's split plane
+  if ((long long)mf_chunks(g) * 128 * g.HW >= (1LL << 31)) return false;
+  MfGeo m;
+  if (!mf_tile(g, &m)) return false;
+  return (long long)g.B * g.T * g.HD <= 65535 &&
+         (long long)m.tiles_x * m.tiles_y * g.B * g.HD * g.T <= 0x7fffffffLL;
+}
+
+static size_t mf_align(size_t b) { return (b + 255) & ~(size_t)255; }
+static size_t mf_plane_bytes(const Geo& g) { return mf_align((size_t)g.B * g.T * g.HD * (size_t)g.HW * mf_chunks(g) * 128); }
+static size_t mf_scale_bytes(const Geo& g) { return mf_align((size_t)g.B * g.T * g.HD * (size_t)g.HW * 4); }
+
+// Per image: its statistics and its scale.
+static size_t mf_info_bytes(const Geo& g) {
+  return mf_align((size_t)g.B * g.T * g.HD * (kStatBlocks * sizeof(float2) + sizeof(float)));
+}
+
+// Split copies and scales of q and k.
+size_t mfma_ws_bytes(const Geo& g) { return 2 * (mf_plane_bytes(g) + mf_scale_bytes(g) + mf_info_bytes(g)); }
+
+snls_status launch_mfma_scores(const float* q, const float* k, const float* flows, const Geo& g, float* scores,
+                               int pitch, void* ws, hipStream_t s) {
+  MfGeo m;
+  if (!mf_tile(g, &m)) return SNLS_ERR_UNSUPPORTED;
+  const long long nwg = (long long)m.tiles_x * m.tiles_y * g.B * g.HD * g.T;
+  if (nwg == 0) return SNLS_OK;
+  struct Split {
+    unsigned char* planes;
+    float *scale, *info;
+  };
+  unsigned char* at = static_cast<unsigned char*>(ws);
+  const unsigned nslab = (unsigned)(g.B * g.T * g.HD);
+  auto split = [&](const float* x) {
+    Split r;
+    r.planes = at;
+    at += mf_plane_bytes(g);
+    r.scale = reinterpret_cast<float*>(at);
+    at += mf_scale_bytes(g);
+    float2* stats = reinterpret_cast<float2*>(at);
+    r.info = reinterpret_cast<float*>(stats + (size_t)nslab * kStatBlocks);
+    at += mf_info_bytes(g);
+    const unsigned nblk = (unsigned)((g.HW + 63) / 64);
+    const unsigned nst = (unsigned)((g.HW + 255) / 256);
+    const unsigned nstat = nst < (unsigned)kStatBlocks ? nst : (unsigned)kStatBlocks;
+    hipLaunchKernelGGL(mf_stats_kernel, dim3(nstat, nslab), dim3(256), 0, s, x, g, stats);
+    hipLaunchKernelGGL(mf_split_kernel, dim3(nblk, nslab), dim3(256), 0, s, x, g, m.nc32, stats, (int)nstat, r.planes,
+                       r.scale, r.info);
+    return r;
+  };
+  const Split ksp = split(k);
+  const Split qsp = q == k ? ksp : split(q);  // one video matched with itself: one copy serves both
+  const dim3 grid((unsigned)nwg), block(mf::waves(m.nc32 > 1 ? 2 : 1) * 64);
+  switch (4 * g.ps + (m.nc32 > 1 ? 2 : 0) + (g.s0 == 1 ? 1 : 0)) {
+#define SNLS_MF_LAUNCH(P, C, S)                                                                                    \
+  hipLaunchKernelGGL((search_mfma_scores_kernel<P, C, S>), grid, block, 0, s, q, k, qsp.planes, qsp.scale,   \
+                     qsp.info, ksp.planes, ksp.scale, ksp.info, flows, g, m, scores, pitch);                                                                               \
+  break
+#define SNLS_MF_CASE(P)                         \
+  case 4 * P: SNLS_MF_LAUNCH(P, 1, false);      \
+  case 4 * P + 1: SNLS_MF_LAUNCH(P, 1, true);   \
+  case 4 * P + 2: SNLS_MF_LAUNCH(P, 2, false);  \
+  case 4 * P + 3: SNLS_MF_LAUNCH(P, 2, true);
+    SNLS_MF_CASE(1)
+    SNLS_MF_CASE(2)
+    SNLS_MF_CASE(3)
+    SNLS_MF_CASE(4)
+    SNLS_MF_CASE(5)
+    SNLS_MF_CASE(6)
+    SNLS_MF_CASE(7)
+#undef SNLS_MF_CASE
+#undef SNLS_MF_LAUNCH
+    default:
+      return SNLS_ERR_UNSUPPORTED;
+  }
+  return hipGetLastError() == hipSuccess ? SNLS_OK : SNLS_ERR_HIP;
+}
+
+}  // namespace snls

@@ -2,6 +2,11 @@
 // candidate for the inner product (key stride S_K <= 1, any query stride),
 // then the top-k of the scored rows (Sec. 3.2).
 //
+// The scores kernel here runs on the vector units in fp32.  Heads of 8 or
+// more channels are scored on the matrix cores instead (search_mfma.hip, same
+// decomposition); this one remains for narrower heads, whose channels would
+// be padded to 32 there, and for frames past that kernel's 32-bit offsets.
+//
 // Window cell d of a query sits at displacement disp_d = F + S_K (d - r);
 // with n_d = floor(disp_d) and a_d = disp_d - n_d its bilinear score is an
 // exact 4-tap combination
@@ -946,12 +951,14 @@ static int tile_ws_pitch(const Geo& g) { return (g.ncand + 31) & ~31; }
 static size_t tile_plane_bytes(const Geo& g) {
   return ((size_t)g.rows * (size_t)tile_ws_pitch(g) * sizeof(float) + 255) & ~(size_t)255;
 }
-size_t tile_ws_bytes(const Geo& g) {
+// The split copies of the matrix-core scores come last.
+static size_t tile_base_bytes(const Geo& g) {
   size_t b = tile_plane_bytes(g);                             // inner-product scores
   if (g.dist == SNLS_DIST_L2)  // key and query norm terms, key pair planes
     b += tile_plane_bytes(g) + (((size_t)g.rows * sizeof(float) + 255) & ~(size_t)255) + l2_planes_bytes(g);
   return b;
 }
+size_t tile_ws_bytes(const Geo& g) { return tile_base_bytes(g) + (mfma_supported(g) ? mfma_ws_bytes(g) : 0); }
 
 // Top-k of the scored rows (any scores kernel of the tiled family).
 static snls_status launch_tile_topk(const float* scores, const float* gnorm, const float* qnorm, int pitch,
@@ -1001,8 +1008,8 @@ snls_status launch_search_p1(const float* q, const float* k, const float* flows,
   return launch_tile_topk(scores, nullptr, nullptr, pitch, flows, g, dists, inds, s);
 }
 
-snls_status launch_search_tile(const float* q, const float* k, const float* flows, const Geo& g, float* dists,
-                               float* inds, float* scores, hipStream_t s) {
+static snls_status launch_tile_scores(const float* q, const float* k, const float* flows, const Geo& g, float* scores,
+                                      int pitch, hipStream_t s) {
   // tile of tqh x tqw queries (the kernel derives the same from S_Q)
   const int tqh = (tile::HROWS - g.ps) / g.s0 + 1, tqw = (tile::TQW - 1) / g.s0 + 1;
   const int tiles_x = (g.nW + tqw - 1) / tqw;
@@ -1014,12 +1021,12 @@ snls_status launch_search_tile(const float* q, const float* k, const float* flow
   switch (g.ws > tile::WSMAX ? 0 : g.ps) {
     case 0:  // P = 7 with a window above 9 (tile_supported)
       hipLaunchKernelGGL((search_tile_scores_kernel<7, tile::WSBIG>), grid, block, 0, s, q, k, flows, g, tiles_x,
-                         tiles_y, scores, tile_ws_pitch(g));
+                         tiles_y, scores, pitch);
       break;
 #define SNLS_TILE_CASE(P)                                                                                       \
   case P:                                                                                                       \
     hipLaunchKernelGGL((search_tile_scores_kernel<P, tile::WSMAX>), grid, block, 0, s, q, k, flows, g, tiles_x, \
-                       tiles_y, scores, tile_ws_pitch(g));                                                      \
+                       tiles_y, scores, pitch);                                                                 \
     break;
     SNLS_TILE_CASE(1)
     SNLS_TILE_CASE(2)
@@ -1032,7 +1039,20 @@ snls_status launch_search_tile(const float* q, const float* k, const float* flow
     default:
       return SNLS_ERR_UNSUPPORTED;
   }
+  return hipGetLastError() == hipSuccess ? SNLS_OK : SNLS_ERR_HIP;
+}
+
+snls_status launch_search_tile(const float* q, const float* k, const float* flows, const Geo& g, float* dists,
+                               float* inds, float* scores, hipStream_t s) {
   const int pitch = tile_ws_pitch(g);
+  if (mfma_supported(g)) {
+    const snls_status st = launch_mfma_scores(q, k, flows, g, scores, pitch,
+                                              reinterpret_cast<char*>(scores) + tile_base_bytes(g), s);
+    if (st != SNLS_OK) return st;
+  } else {
+    const snls_status st = launch_tile_scores(q, k, flows, g, scores, pitch, s);
+    if (st != SNLS_OK) return st;
+  }
   float* gnorm = nullptr;
   float* qnorm = nullptr;
   if (g.dist == SNLS_DIST_L2) {

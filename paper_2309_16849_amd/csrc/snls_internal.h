@@ -63,6 +63,10 @@ size_t gather_ws_bytes(const Geo& g);
 // term of every candidate and the query-norm term of every row.
 bool tile_supported(const Geo& g);
 size_t tile_ws_bytes(const Geo& g);
+// The tiled route's scores on the matrix cores (8 channels per head or more)
+// and the split copies of q and k they read (part of tile_ws_bytes).
+bool mfma_supported(const Geo& g);
+size_t mfma_ws_bytes(const Geo& g);
 // Single-pixel patches (P = 1), any S_Q, S_K = 1, inner product, Ws <= 15:
 // same workspace layout (scores of every candidate) for k > 32; for k <= 32
 // (p1_fused) the selection runs inside the scoring kernel, no workspace.
@@ -90,6 +94,8 @@ snls_status launch_search_p1_scores(const float* q, const float* k, const float*
                                     int pitch, hipStream_t s);
 snls_status launch_search_p1_topk(const float* q, const float* k, const float* flows, const Geo& g, float* dists,
                                   float* inds, hipStream_t s);
+snls_status launch_mfma_scores(const float* q, const float* k, const float* flows, const Geo& g, float* scores,
+                               int pitch, void* ws, hipStream_t s);
 // L2 norm terms: key pair planes (workspace of l2_planes_bytes(g) bytes),
 // then the key-norm terms G (rows x pitch) and the query norms Qn (rows).
 size_t l2_planes_bytes(const Geo& g);

@@ -1,0 +1,92 @@
+"""The matrix-core scores of the tiled search against the oracle where the
+kernel changes path: channel padding and chunk groups (8 to 130 channels per
+head), unions of shift columns at the edges of two and three key blocks and of
+the three lane layouts (17/18, 21/22, 32/33 columns), more shift rows than one
+round holds, strided queries, every patch size, and images whose pixels need
+scales of their own."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2309_16849_amd import snls as B
+from tests.parity import compare_topk
+from workloads import small_params
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    B.load_library()
+    return torch.device("cuda:0")
+
+
+def _flows(p, rows, cols, rng):
+    """Offsets whose integer parts spread over `rows` x `cols` shifts in every tile."""
+    shp = (p["B"], p["T"], 2 * p["wt"], p["H"], p["W"])
+    y, x = np.mgrid[0:p["H"], 0:p["W"]]
+    fl = np.empty(shp[:3] + (2,) + shp[3:], np.float32)
+    fl[:, :, :, 0] = 0.3 - rows // 2 + (y * 5 + x) % (rows + 1)
+    fl[:, :, :, 1] = 0.6 - cols // 2 + (y + x * 3) % (cols + 1)
+    return (fl + rng.uniform(-0.2, 0.2, fl.shape)).astype(np.float32)
+
+
+def _search(q, k, fl, p, dev):
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    gd, gi = B.snls_search(d(q), d(k), d(fl), p)
+    torch.cuda.synchronize()
+    return gd.cpu().numpy().reshape(-1, p["k"]), gi.cpu().numpy().reshape(-1, p["k"], 3)
+
+
+CASES = [  # patch, channels, heads, window, query stride, key stride, spread of rows and columns
+    (7, 8, 1, 9, 1, 1.0, 4, 7), (7, 64, 1, 9, 1, 1.0, 6, 8), (7, 65, 1, 9, 1, 1.0, 14, 11), (3, 33, 1, 9, 1, 1.0, 7, 12),
+    (5, 130, 1, 5, 1, 0.5, 3, 18), (7, 96, 3, 9, 1, 1.0, 26, 22), (1, 32, 1, 9, 1, 0.5, 5, 27), (2, 24, 2, 7, 1, 1.0, 9, 24),
+    (4, 16, 1, 8, 2, 1.0, 8, 11), (6, 40, 1, 9, 3, 0.75, 5, 6), (7, 16, 1, 15, 1, 1.0, 3, 3), (7, 72, 1, 13, 2, 1.0, 9, 19),
+]
+
+
+@pytest.mark.parametrize("ps,C,HD,ws,s0,s1,rows,cols", CASES)
+def test_scores_at_path_edges(dev, ps, C, HD, ws, s0, s1, rows, cols):
+    p = small_params(T=2, C=C, HD=HD, H=38, W=43, ws=ws, wt=1, ps=ps, k=12, stride0=s0, stride1=s1)
+    rng = np.random.default_rng(ps * 1000 + C)
+    shp = (1, 2, C, 38, 43)
+    q, k = (rng.standard_normal(shp, dtype=np.float32) for _ in range(2))
+    fl = _flows(p, rows, cols, rng)
+    gd, gi = _search(q, k, fl, p, dev)
+    compare_topk(gd, gi, oracle.search(q, k, fl, p), p["k"])
+
+
+@pytest.mark.parametrize("which", ["q", "k", "both"])
+def test_pixels_with_scales_of_their_own(dev, which):
+    """Pixels from 1e-12 to 1e12 in one image: each score is compared with
+    the largest score its own row could have, so that a lost low-magnitude
+    pixel would show (22-bit operands: 1e-6 of the row's scale)."""
+    p = small_params(T=2, C=24, H=30, W=33, ws=5, wt=1, ps=1, k=33)
+    rng = np.random.default_rng(77)
+    shp = (1, 2, 24, 30, 33)
+    q, k = (rng.standard_normal(shp, dtype=np.float32) for _ in range(2))
+    mag = (10.0 ** rng.integers(-12, 13, (1, 2, 1, 30, 33))).astype(np.float32)
+    if which != "k":
+        q = q * mag
+    if which != "q":
+        k = k * mag
+    fl = rng.integers(-2, 3, (1, 2, 2, 2, 30, 33)).astype(np.float32)
+    gd, gi = _search(q, k, fl, p, dev)
+    res = oracle.search(q, k, fl, p)
+    ref = res["dists"][:, :33]
+    fin = np.isfinite(ref)
+    assert np.array_equal(fin, np.isfinite(gd))
+    err = np.abs(np.where(fin, gd, 0.0) - np.where(fin, ref, 0.0))
+    # |q| |k~| of the candidate bounds the sum of its products' magnitudes
+    qn = np.sqrt((q.astype(np.float64) ** 2).sum(2)).reshape(-1)
+    kn = np.sqrt((k.astype(np.float64) ** 2).sum(2))[0]
+    y, x = np.mgrid[0:30, 0:33]
+    at = gi.reshape(2, 30, 33, 33, 3)
+    f = at[..., 0].astype(int)
+    Y = np.clip(y[None, :, :, None] + at[..., 1], 0, 29).astype(int)
+    X = np.clip(x[None, :, :, None] + at[..., 2], 0, 32).astype(int)
+    bound = qn[:, None] * kn[np.clip(f, 0, 1), Y, X].reshape(-1, 33)
+    assert (err <= 1e-6 * bound + 1e-30)[fin].all()

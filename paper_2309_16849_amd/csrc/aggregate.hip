@@ -14,7 +14,7 @@
 // position for 64 channels) and accumulated.
 //
 // Kernels: softmax weights per (row, neighbour); transpose of V to
-// (B,T,H,W,C); the tiled gather (query stride 1); the merged gather; the
+// (B,T,H,W,C); the tiled gather (any query stride); the merged gather; the
 // per-query gather of single-pixel patches (any query stride); plus the
 // plain per-tap gather used when a configuration exceeds the other kernels'
 // limits.
@@ -362,6 +362,8 @@ constexpr int BOX = 8;               // offsets per axis and slot
 constexpr int SB = BOX * BOX;        // bins per slot (one per lane)
 constexpr int MAXREC = 2048;         // (covering query, neighbour) records per tile
 constexpr int MAXQ = 256;            // covering queries per tile
+constexpr int LCAP = 128;            // positions gathered at a time (at most 64 are added at once)
+constexpr int CMAX = 256;            // channels per head (16-byte lanes of one wave)
 constexpr float QSCALE = 16777216.f; // fixed point 2^24
 static_assert(MAXREC <= WAVES * 64 * (TX + 1), "the covering queries' scores fit in the output buffer");
 }  // namespace aggt
@@ -369,25 +371,41 @@ static_assert(MAXREC <= WAVES * 64 * (TX + 1), "the covering queries' scores fit
 // floor(a / s) for s > 0 and any sign of a
 SNLS_DEV int floor_div(int a, int s) { return a >= 0 ? a / s : -((-a + s - 1) / s); }
 
+// Gather of the listed positions.  With channels in multiples of 4 a lane
+// reads 16 bytes, so 2^lb lanes cover a position's channel vector and one
+// load of the wave covers 64 >> lb positions (4 at 64 channels); four such
+// loads are in flight, and the partial sums of the lane groups are added at
+// the end of the pixel.  (One channel per lane and two positions in flight,
+// left the wave waiting for each pair.  Bound by the L2 reads of V -- about
+// 60 to 100 positions of 256 bytes a pixel; 480x854, 64 channels, P = 7, soft
+// weights: 7.95 -> 3.4 ms, 256x256: 1.28 -> 0.59 ms; 152x152 with 192
+// channels, which took the per-pixel merging kernel: 3.23 -> 0.55 ms.)
+//
+// Records outside the bin boxes (offsets scattered over more than 8 x 8
+// positions, frames outside the window) add their four taps to the same list,
+// a lane per record; one at a time by the whole wave they took 0.36 ms of the
+// 64 x 64 noise clip.
+//
 // SQ: the query stride when known at compile time (1), else 0 (g.s0).
-// GW: bin positions gathered per pass (their channel-vector loads in flight
-// together): 4 for patches up to 5 x 5, 2 for larger ones (measured faster
-// each way on the 256 x 256 P = 3 and 480 x 854 P = 7 workloads).
-template <int SQ, int GW>
+// VEC: channels per head a multiple of 4.  REC, NS, CB: capacities for records,
+// frame slots and channels; the smallest that hold the call let two
+// workgroups share a CU (80 KB each).
+template <int SQ, bool VEC, int REC, int NS, int CB>
 __global__ void __launch_bounds__(aggt::NT) aggregate_tile_kernel(const float* __restrict__ vcl,
                                                                   const float* __restrict__ dists,
                                                                   const float* __restrict__ inds, Geo g,
-                                                                  float scale, int tiles_x, int tiles_y,
+                                                                  float scale, int tiles_x, int tiles_y, int lb,
                                                                   float* __restrict__ out) {
   using namespace aggt;
-  __shared__ int4 rtap[MAXREC];     // fixed-point tap weights (0,0) (0,1) (1,0) (1,1)
-  __shared__ int rcode[MAXREC];     // bin of tap (0,0); -1 nothing; -2 direct path
+  __shared__ int4 rtap[REC];        // fixed-point tap weights (0,0) (0,1) (1,0) (1,1)
+  __shared__ int rcode[REC];        // bin of tap (0,0); -1 nothing; -2 direct path
   __shared__ float qm[MAXQ], qinv[MAXQ];  // softmax max and 1/sum per covering query
   __shared__ int sstat[3 * NSLOT];  // per slot: sum of row offsets, of column offsets, count
   __shared__ int sbase[2 * NSLOT];  // per slot: box origin (row, column offset)
   __shared__ int ndirect;           // records of the tile outside the bin boxes
-  __shared__ int bins[WAVES][NSLOT * SB];
-  __shared__ float obuf[WAVES][64][TX + 1];
+  __shared__ int bins[WAVES][NS * SB];
+  __shared__ float obuf[WAVES][CB][TX + 1];
+  __shared__ int2 plist[WAVES][LCAP];  // positions to gather: offset in vcl, weight
 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   // XCD-aware order: each XCD takes a contiguous run of tiles (neighbouring
@@ -409,7 +427,7 @@ __global__ void __launch_bounds__(aggt::NT) aggregate_tile_kernel(const float* _
   const float sscale = (g.dist == SNLS_DIST_PROD ? 1.f : -1.f) * scale;
   const long long rowb = (((long long)b * g.HD + hd) * g.T + t) * g.nH;
 
-  for (int i = tid; i < WAVES * NSLOT * SB; i += NT) (&bins[0][0])[i] = 0;
+  for (int i = tid; i < WAVES * NS * SB; i += NT) (&bins[0][0])[i] = 0;
   if (tid < 3 * NSLOT) sstat[tid] = 0;
   if (tid == 0) ndirect = 0;
 
@@ -549,7 +567,7 @@ __global__ void __launch_bounds__(aggt::NT) aggregate_tile_kernel(const float* _
   unsigned slots = 0;  // slots with entries in the tile (wave-uniform)
   for (int s = 0; s < nslot; ++s)
     if (sstat[2 * NSLOT + s] != 0) slots |= 1u << s;
-  const bool any_direct = ndirect != 0;
+  const bool any_direct = ndirect != 0;  // (wave-uniform)
   int* const wbins = bins[wv];
   // add (sign +1) or remove (-1) the records of query columns c0 .. c0+nc-1
   auto slide = [&](int c0, int nc, int sign) {
@@ -570,11 +588,74 @@ __global__ void __launch_bounds__(aggt::NT) aggregate_tile_kernel(const float* _
       }
     }
   };
+  // gather of the n listed positions into this lane's channels
+  int2* const pl = plist[wv];
+  const int grp = VEC ? lane >> lb : 0, sub = VEC ? lane & ((1 << lb) - 1) : lane;
+  const int npos = VEC ? 64 >> lb : 1;            // positions per load
+  const bool chan = VEC ? 4 * sub < g.Ch : lane < g.Ch;
+  float acc[VEC ? 4 : 1];
+  int nl = 0;  // listed positions (wave-uniform)
+  const float* const vlane = vb + (VEC ? 4 * sub : lane);
+  auto gather = [&]() {
+    wave_lds_sync();
+    if (chan) {
+      int i = 0;
+      for (; i + 4 * npos <= nl; i += 4 * npos) {
+        int2 e[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) e[u] = pl[i + u * npos + grp];
+        if constexpr (VEC) {
+          float4 a[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) a[u] = *reinterpret_cast<const float4*>(vlane + e[u].x);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const float w = __int_as_float(e[u].y);
+            acc[0] = fmaf(w, a[u].x, acc[0]);
+            acc[1] = fmaf(w, a[u].y, acc[1]);
+            acc[2] = fmaf(w, a[u].z, acc[2]);
+            acc[3] = fmaf(w, a[u].w, acc[3]);
+          }
+        } else {
+          float a[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) a[u] = vlane[e[u].x];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) acc[0] = fmaf(__int_as_float(e[u].y), a[u], acc[0]);
+        }
+      }
+      for (; i < nl; i += npos) {
+        if (i + grp < nl) {
+          const int2 e = pl[i + grp];
+          const float w = __int_as_float(e.y);
+          if constexpr (VEC) {
+            const float4 a = *reinterpret_cast<const float4*>(vlane + e.x);
+            acc[0] = fmaf(w, a.x, acc[0]);
+            acc[1] = fmaf(w, a.y, acc[1]);
+            acc[2] = fmaf(w, a.z, acc[2]);
+            acc[3] = fmaf(w, a.w, acc[3]);
+          } else {
+            acc[0] = fmaf(w, vlane[e.x], acc[0]);
+          }
+        }
+      }
+    }
+    nl = 0;
+    wave_lds_sync();
+  };
+  // one position per lane with `has`, in lane order
+  auto list = [&](bool has, int off, float w) {
+    const unsigned long long m = __ballot(has);
+    if (has) pl[nl + lanes_below(m)] = make_int2(off, __float_as_int(w));
+    nl += __popcll(m);
+    if (nl > LCAP - 64) gather();
+  };
   int pa = 0, pb = -1;  // query columns in the bins
   for (int px = 0; px < TX; ++px) {
     const int x = x0 + px;
     if (y >= g.H || x >= g.W) break;  // wave-uniform
-    float acc = 0.f;
+#pragma unroll
+    for (int i = 0; i < (VEC ? 4 : 1); ++i) acc[i] = 0.f;
     const int ca = floor_div(x - g.lo - P + 1 + s0 - 1, s0) - wq0, cb = floor_div(x - g.lo, s0) - wq0;
     if constexpr (SQ == 1) {  // columns px .. px+P-1: all P at the first pixel, then one in, one out
       if (px == 0) {
@@ -592,7 +673,7 @@ __global__ void __launch_bounds__(aggt::NT) aggregate_tile_kernel(const float* _
       pb = cb;
     }
     if (any_direct) {
-      // neighbours outside the bin boxes: the whole wave reads their taps directly
+      // neighbours outside the bin boxes: a lane per record, tap by tap
       const int ncov = (cb - ca + 1) * RK;
       for (int e0 = 0; e0 < ncov; e0 += 64) {
         const int e = e0 + lane;
@@ -601,73 +682,45 @@ __global__ void __launch_bounds__(aggt::NT) aggregate_tile_kernel(const float* _
         const int qy = (int)(((float)rem + 0.5f) * inv_k);
         const int l = rem - qy * K;
         const int ri = ((ra + qy) * QX + ca + cc) * K + l;
-        const int code = e < ncov ? rcode[ri] : -1;
-        unsigned long long om = __ballot(code == -2);
-        while (om) {
-          const int src = __ffsll((long long)om) - 1;
-          om &= om - 1;
-          const int e_ = __builtin_amdgcn_readlane(ri, src);
-          float wl, ah, aw;
-          int t2, nh, nw;
-          neighbour(e_, wl, t2, nh, nw, ah, aw, false);
-          const float* vf = vb + (long long)t2 * g.HW * g.C;
+        const bool dir = e < ncov && rcode[ri] == -2;
+        if (__ballot(dir) == 0) continue;
+        float wl = 0.f, ah = 0.f, aw = 0.f;
+        int t2 = 0, nh = 0, nw = 0;
+        if (dir) neighbour(ri, wl, t2, nh, nw, ah, aw, false);
 #pragma unroll
-          for (int eh = 0; eh < 2; ++eh)
+        for (int eh = 0; eh < 2; ++eh)
 #pragma unroll
-            for (int ew = 0; ew < 2; ++ew) {
-              const int Y = y + nh + eh, X = x + nw + ew;
-              const float tw = wl * (eh ? ah : 1.f - ah) * (ew ? aw : 1.f - aw);
-              if (Y >= 0 && Y < g.H && X >= 0 && X < g.W && tw != 0.f && lane < g.Ch)
-                acc = fmaf(tw, vf[((long long)Y * g.W + X) * g.C + lane], acc);
-            }
-        }
+          for (int ew = 0; ew < 2; ++ew) {
+            const int Y = y + nh + eh, X = x + nw + ew;
+            const float tw = wl * (eh ? ah : 1.f - ah) * (ew ? aw : 1.f - aw);
+            list(dir && Y >= 0 && Y < g.H && X >= 0 && X < g.W && tw != 0.f, ((t2 * g.H + Y) * g.W + X) * g.C, tw);
+          }
       }
     }
     wave_lds_sync();
-    // non-empty bins in bin order: one channel-vector read per position
+    // non-empty bins in bin order
     for (int s = 0; s < nslot; ++s) {
       if (!(slots & (1u << s))) continue;
       const int v = wbins[s * SB + lane];
       const int Y = y + sbase[s] + (lane >> 3), X = x + sbase[NSLOT + s] + (lane & 7);
-      const bool nz = v != 0 && Y >= 0 && Y < g.H && X >= 0 && X < g.W;
-      const int off = ((t + s - g.wt) * (int)g.HW + Y * g.W + X) * g.C;
-      const float wgt = (float)v * (1.f / QSCALE);
-      unsigned long long m = __ballot(nz);
-      // up to GW positions per pass (in bin order), their loads in flight
-      // together; the pass's count n is wave-uniform, and a padded slot
-      // re-reads the first position and adds nothing
-      while (m) {
-        int sl[GW];
-        int n = 0;
-#pragma unroll
-        for (int i = 0; i < GW; ++i) {
-          sl[i] = m ? __ffsll((long long)m) - 1 : sl[0];
-          if (m) {
-            m &= m - 1;
-            ++n;
-          }
-        }
-        float wv[GW];
-        int ov[GW];
-#pragma unroll
-        for (int i = 0; i < GW; ++i) {
-          wv[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wgt), sl[i]));
-          ov[i] = __builtin_amdgcn_readlane(off, sl[i]);
-        }
-        if (lane < g.Ch) {
-          float a[GW];
-#pragma unroll
-          for (int i = 0; i < GW; ++i) a[i] = vb[ov[i] + lane];
-#pragma unroll
-          for (int i = 0; i < GW; ++i)
-            if (i < n) acc = fmaf(wv[i], a[i], acc);
-        }
-      }
+      list(v != 0 && Y >= 0 && Y < g.H && X >= 0 && X < g.W, ((t + s - g.wt) * (int)g.HW + Y * g.W + X) * g.C,
+           (float)v * (1.f / QSCALE));
     }
-    wave_lds_sync();
+    gather();
     const int cnt = cov_y * cover_count_1d(x, s0, g.nW, g.lo, P);
-    obuf[wv][lane][px] = cnt > 0 ? acc * (1.f / (float)cnt) : 0.f;
+    const float inv = cnt > 0 ? 1.f / (float)cnt : 0.f;
+    if constexpr (VEC) {
+      for (int o = 1 << lb; o < 64; o <<= 1)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] += __shfl_xor(acc[i], o);
+      if (grp == 0 && chan)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) obuf[wv][4 * sub + i][px] = cnt > 0 ? acc[i] * inv : 0.f;
+    } else {
+      obuf[wv][lane][px] = cnt > 0 ? acc[0] * inv : 0.f;
+    }
   }
+  wave_lds_sync();
   // write the row: TX consecutive pixels per channel
   if (y < g.H) {
     const int nx = min(TX, g.W - x0);
@@ -978,27 +1031,34 @@ snls_status launch_aggregate(const float* v, const float* dists, const float* in
   // fixed point (at most P^2 <= 121 covering patches)
   const long long nq_tile =
       (long long)((aggt::TY + g.ps - 2) / g.s0 + 1) * ((aggt::TX + g.ps - 2) / g.s0 + 1);  // covering queries
-  if (nslot <= aggt::NSLOT && g.Ch <= 64 && (long long)g.T * g.HW * g.C < (1LL << 31) &&
+  const bool vec = g.Ch % 4 == 0;
+  if (nslot <= aggt::NSLOT && g.Ch <= (vec ? aggt::CMAX : 64) && (long long)g.T * g.HW * g.C < (1LL << 31) &&
       g.ps <= 11 && nq_tile <= aggt::MAXQ && nq_tile * g.k <= aggt::MAXREC) {
-    dim3 tgrid((unsigned)((g.HW + 63) / 64), (unsigned)((g.C + 63) / 64), (unsigned)(g.B * g.T));
-    if (g.C % 4 == 0 && (long long)g.HW * 4 < (1LL << 31))
-      hipLaunchKernelGGL(to_channels_last4_kernel<false>, tgrid, dim3(256), 0, s, v, g, vcl);
-    else
-      hipLaunchKernelGGL(to_channels_last_kernel, tgrid, dim3(256), 0, s, v, g, vcl);
+    const snls_status st = launch_to_channels_last(v, g, vcl, s);
+    if (st != SNLS_OK) return st;
     const int tiles_x = (g.W + aggt::TX - 1) / aggt::TX, tiles_y = (g.H + aggt::TY - 1) / aggt::TY;
     const long long nwg = (long long)tiles_x * tiles_y * g.B * g.T * g.HD;
     if (nwg > 0x7fffffffLL) return SNLS_ERR_UNSUPPORTED;
-#define SNLS_AGGT(SQ, GW)                                                                                    \
-  hipLaunchKernelGGL((aggregate_tile_kernel<SQ, GW>), dim3((unsigned)nwg), dim3(aggt::NT), 0, s, vcl, dists, inds, \
-                     g, scale, tiles_x, tiles_y, out)
-    if (g.s0 == 1) {
-      if (g.ps <= 5) SNLS_AGGT(1, 4);
-      else SNLS_AGGT(1, 2);
-    } else {
-      if (g.ps <= 5) SNLS_AGGT(0, 4);
-      else SNLS_AGGT(0, 2);
-    }
+    int lb = 0;  // 2^lb 16-byte lanes cover a head's channels
+    while ((4 << lb) < g.Ch) ++lb;
+    const bool rec_s = nq_tile * g.k <= 1024, ns_s = nslot <= 5;
+    // records are at most REC; the scores of phase 1 sit in the output buffer
+#define SNLS_AGGT(SQ, V, R, N, C)                                                                                 \
+  hipLaunchKernelGGL((aggregate_tile_kernel<SQ, V, R, N, C>), dim3((unsigned)nwg), dim3(aggt::NT), 0, s, vcl, dists, \
+                     inds, g, scale, tiles_x, tiles_y, lb, out)
+#define SNLS_AGGT_CAP(SQ, V, C)                      \
+  if (rec_s && ns_s) SNLS_AGGT(SQ, V, 1024, 5, C);   \
+  else if (ns_s) SNLS_AGGT(SQ, V, 2048, 5, C);       \
+  else SNLS_AGGT(SQ, V, 2048, 7, C);
+#define SNLS_AGGT_CH(SQ)                               \
+  if (!vec) { SNLS_AGGT_CAP(SQ, false, 64) }           \
+  else if (g.Ch <= 64) { SNLS_AGGT_CAP(SQ, true, 64) } \
+  else { SNLS_AGGT(SQ, true, 2048, 7, 256); }
+    if (g.s0 == 1) { SNLS_AGGT_CH(1) }
+    else { SNLS_AGGT_CH(0) }
 #undef SNLS_AGGT
+#undef SNLS_AGGT_CAP
+#undef SNLS_AGGT_CH
     return hipGetLastError() == hipSuccess ? SNLS_OK : SNLS_ERR_HIP;
   }
   {

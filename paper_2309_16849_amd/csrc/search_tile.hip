@@ -49,6 +49,7 @@
 // A second kernel then streams each query row's scores once and keeps its
 // top k (Sec. 3.2 top-L over the whole space-time window), so the
 // correlation kernel carries no per-query selection state.
+#include "row16.h"
 #include "snls_internal.h"
 
 namespace snls {
@@ -932,6 +933,204 @@ __global__ void __launch_bounds__(wtk::WAVES * 64) wave_topk_kernel(const float*
   irow[2] = cand_disp(fw, g.s1, dw, g.r);
 }
 
+// ---- exact top-k, 16 lanes per scored row (k <= 16, <= 64 * NV candidates) ----
+//
+// Lane l of a row's 16 holds candidates 64 v + 4 l .. + 3 (16-byte loads, 256
+// bytes a row and pass) as order keys.  The k-th largest of 32 maxima (two
+// halves of each lane's candidates) bounds the row's k-th best from below; the
+// candidates that reach it (about 12 at k = 10) go to the row's 32 LDS slots and are sorted with a 32-entry
+// bitonic network by (score descending, id ascending).  When more than 32
+// reach it (ties, rows with many invalid candidates), the exact k-th key is
+// found by bisection and the ties of smallest id complete the k.
+//
+// One thread per row (tile_topk_kernel) runs 64 rows in step but waits for
+// each row's next 128 bytes.  Thread per row against this kernel: 2,049,600
+// rows of 405 candidates (480x854) 1.11 and 0.86 ms, 81,920 rows (L2) 184 and
+// 61 us, 12,288 rows of 243 (64x64) 96 and 9 us, 115,520 rows of 45 41 and 44
+// us.  Bound by its own instructions, about 320 per row.
+namespace gtk {
+constexpr int ROWS = 16;    // rows per workgroup
+constexpr int SLOTS = 32;
+constexpr int KMAX = 16;    // beyond it the bound lets too many through
+}  // namespace gtk
+
+// Descending sort of two keys per lane across the 16 lanes (element 2 l + half).
+template <int SIZE, int STRIDE>
+SNLS_DEV void key_stage32(unsigned& x0, unsigned& x1, int l) {
+  const bool desc = ((2 * l) & SIZE) == 0;
+  if constexpr (STRIDE == 1) {
+    const unsigned hi = max(x0, x1), lo = min(x0, x1);
+    x0 = desc ? hi : lo;
+    x1 = desc ? lo : hi;
+  } else {
+    constexpr int LM = STRIDE / 2;  // partner lane distance
+    const unsigned p0 = grp_xor<LM>(x0, l), p1 = grp_xor<LM>(x1, l);
+    const bool keep_max = ((l & LM) == 0) == desc;
+    x0 = keep_max ? max(x0, p0) : min(x0, p0);
+    x1 = keep_max ? max(x1, p1) : min(x1, p1);
+  }
+}
+SNLS_DEV void sort32_keys(unsigned& x0, unsigned& x1, int l) {
+  key_stage32<2, 1>(x0, x1, l);
+  key_stage32<4, 2>(x0, x1, l);
+  key_stage32<4, 1>(x0, x1, l);
+  key_stage32<8, 4>(x0, x1, l);
+  key_stage32<8, 2>(x0, x1, l);
+  key_stage32<8, 1>(x0, x1, l);
+  key_stage32<16, 8>(x0, x1, l);
+  key_stage32<16, 4>(x0, x1, l);
+  key_stage32<16, 2>(x0, x1, l);
+  key_stage32<16, 1>(x0, x1, l);
+  key_stage32<32, 16>(x0, x1, l);
+  key_stage32<32, 8>(x0, x1, l);
+  key_stage32<32, 4>(x0, x1, l);
+  key_stage32<32, 2>(x0, x1, l);
+  key_stage32<32, 1>(x0, x1, l);
+}
+
+template <int NV>
+__global__ void __launch_bounds__(gtk::ROWS * 16) group_topk_kernel(const float* __restrict__ scores,
+                                                                    const float* __restrict__ gnorm,
+                                                                    const float* __restrict__ qnorm, int pitch,
+                                                                    const float* __restrict__ flows, Geo g,
+                                                                    float* __restrict__ dists,
+                                                                    float* __restrict__ inds) {
+  __shared__ unsigned long long slot[gtk::ROWS][gtk::SLOTS + 1];
+  const int l = threadIdx.x & 15, gi = threadIdx.x >> 4;
+  const unsigned row = blockIdx.x * gtk::ROWS + gi;
+  if (row >= (unsigned)g.rows) return;  // all 16 lanes
+  // query of this row
+  unsigned rr = row;
+  const int w = (int)(rr % (unsigned)g.nW) * g.s0;
+  rr /= (unsigned)g.nW;
+  const int h = (int)(rr % (unsigned)g.nH) * g.s0;
+  rr /= (unsigned)g.nH;
+  const int t = (int)(rr % (unsigned)g.T);
+  const int b = (int)(rr / (unsigned)g.T) / g.HD;
+  const int ncell = g.ws * g.ws;
+  const float* srow = scores + (size_t)row * pitch;
+  const bool l2 = g.dist == SNLS_DIST_L2;
+  const float qn = l2 ? qnorm[row] : 0.f;
+  const float* grow = l2 ? gnorm + (size_t)row * pitch : nullptr;
+  // candidate ids of the frames inside the clip (the others score -inf)
+  const int lo = (max(0, t - g.wt) - t + g.wt) * ncell, hi = (min(g.T - 1, t + g.wt) - t + g.wt + 1) * ncell;
+  float4 v[NV];
+#pragma unroll
+  for (int n = 0; n < NV; ++n) {
+    const int c = 64 * n + 4 * l;
+    v[n] = c + 4 > lo && c < hi ? *reinterpret_cast<const float4*>(srow + c)
+                                : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+  }
+  unsigned u[NV][4];
+  unsigned m0 = 0, m1 = 0;  // largest keys of the lane's two halves
+#pragma unroll
+  for (int n = 0; n < NV; ++n) {
+    const int c = 64 * n + 4 * l;
+    float4 gn = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (l2 && c + 4 > lo && c < hi) gn = *reinterpret_cast<const float4*>(grow + c);
+    const float e[4] = {v[n].x, v[n].y, v[n].z, v[n].w}, ge[4] = {gn.x, gn.y, gn.z, gn.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float sc = e[i];
+      if (l2) {  // minus the squared distance from the inner product and the norm terms (invalid: -inf)
+        const float dd = qn - 2.f * sc + ge[i];
+        sc = sc > -INFINITY && dd == dd ? -dd : -INFINITY;
+      }
+      if (c + i < lo || c + i >= hi) sc = -INFINITY;
+      u[n][i] = c + i < g.ncand ? order_key(sc + 0.f) : 0u;  // (-0 ties with +0; 0: no candidate)
+      if (i < 2) m0 = max(m0, u[n][i]);
+      else m1 = max(m1, u[n][i]);
+    }
+  }
+  const int gb = (threadIdx.x & 63) & ~15;  // the row's first lane in the wave
+  const unsigned umax = max(m0, m1);
+  sort32_keys(m0, m1, l);
+  const unsigned T1 = (unsigned)__shfl((int)(((g.k - 1) & 1) ? m1 : m0), gb + ((g.k - 1) >> 1));
+  unsigned long long* const sl = slot[gi];
+  auto entry = [&](unsigned key, int id) { return ((unsigned long long)key << 32) | (unsigned)(~id); };
+  int cnt = 0;
+#pragma unroll
+  for (int n = 0; n < NV; ++n)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) cnt += u[n][i] >= T1 ? 1 : 0;
+  // (fewer than k halves with a candidate: T1 = 0, every slot would pass)
+  int ntot = grp_sum(cnt);
+  if (T1 != 0u && ntot <= gtk::SLOTS) {
+    int off = grp_excl_scan(cnt);
+#pragma unroll
+    for (int n = 0; n < NV; ++n)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (u[n][i] >= T1) sl[off++] = entry(u[n][i], 64 * n + 4 * l + i);
+  } else {
+    // exact k-th key: the largest x with at least k candidates >= x
+    auto count_ge = [&](unsigned x) {
+      int c = 0;
+#pragma unroll
+      for (int n = 0; n < NV; ++n)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c += u[n][i] >= x ? 1 : 0;
+      return grp_sum(c);
+    };
+    unsigned klo = 1u;  // every candidate's key is at least that of -inf
+    unsigned long long khi = (unsigned long long)grp_max(umax) + 1;
+    while (khi - klo > 1) {
+      const unsigned mid = (unsigned)(klo + (khi - klo) / 2);
+      if (count_ge(mid) >= g.k) klo = mid;
+      else khi = mid;
+    }
+    const int need = g.k - count_ge(klo + 1);  // entries equal to the k-th key
+    int base = 0, eqn = 0;
+#pragma unroll
+    for (int n = 0; n < NV; ++n) {
+      int ne = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ne += u[n][i] == klo ? 1 : 0;
+      int before = eqn + grp_excl_scan(ne);  // ties of smaller id
+      eqn += grp_sum(ne);
+      bool take[4];
+      int nt = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool eq = u[n][i] == klo;
+        take[i] = u[n][i] > klo || (eq && before < need);
+        before += eq ? 1 : 0;
+        nt += take[i] ? 1 : 0;
+      }
+      int off = base + grp_excl_scan(nt);
+      base += grp_sum(nt);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (take[i]) sl[off++] = entry(u[n][i], 64 * n + 4 * l + i);
+    }
+    ntot = base;  // k
+  }
+  wave_lds_sync();
+  unsigned long long s0 = 2 * l < ntot ? sl[2 * l] : 0ull, s1 = 2 * l + 1 < ntot ? sl[2 * l + 1] : 0ull;
+  bitonic_sort32(s0, s1, l);
+  // rank l to lane l
+  const int src = gb + (l >> 1);
+  const unsigned a0 = (unsigned)__shfl((int)(unsigned)s0, src), a1 = (unsigned)__shfl((int)(unsigned)s1, src);
+  const unsigned k0 = (unsigned)__shfl((int)(unsigned)(s0 >> 32), src), k1 = (unsigned)__shfl((int)(unsigned)(s1 >> 32), src);
+  if (l >= g.k) return;
+  // every candidate was ranked, so the k best are real candidates; the clamp
+  // only keeps a placeholder id in bounds
+  const int cid = min(max((int)~((l & 1) ? a1 : a0), 0), g.ncand - 1);
+  const int dw = cid % g.ws, dh = (cid / g.ws) % g.ws, dt = cid / ncell - g.wt;
+  float fh = 0.f, fw = 0.f;
+  if (dt != 0) {
+    const long long pix = (long long)h * g.W + w;
+    const long long base = (((long long)b * g.T + t) * g.nslot + flow_slot(dt, g.wt)) * 2;
+    fh = flows[base * g.HW + pix];
+    fw = flows[(base + 1) * g.HW + pix];
+  }
+  const size_t o = (size_t)row * g.k + l;
+  dists[o] = from_score(key_score((l & 1) ? k1 : k0), g.dist) + 0.f;
+  inds[3 * o] = (float)(t + dt);
+  inds[3 * o + 1] = cand_disp(fh, g.s1, dh, g.r);
+  inds[3 * o + 2] = cand_disp(fw, g.s1, dw, g.r);
+}
+
 // The tiled path handles any S_Q, P <= 7, Ws <= 9 with the inner product
 // (S_K <= 1) or the squared L2 distance (S_K = 1).
 bool tile_supported(const Geo& g) {
@@ -963,6 +1162,23 @@ size_t tile_ws_bytes(const Geo& g) { return tile_base_bytes(g) + (mfma_supported
 // Top-k of the scored rows (any scores kernel of the tiled family).
 static snls_status launch_tile_topk(const float* scores, const float* gnorm, const float* qnorm, int pitch,
                                     const float* flows, const Geo& g, float* dists, float* inds, hipStream_t s) {
+  // Small k: 16 lanes per row while the row fits their registers (64 values a
+  // lane at 1024 candidates).
+  if (g.k <= gtk::KMAX && g.ncand <= 1024 && g.rows < (1LL << 31)) {
+    const unsigned gblocks = (unsigned)((g.rows + gtk::ROWS - 1) / gtk::ROWS);
+    const int n64 = (g.ncand + 63) / 64;
+#define SNLS_GTK(N)                                                                                                 \
+  hipLaunchKernelGGL(group_topk_kernel<N>, dim3(gblocks), dim3(gtk::ROWS * 16), 0, s, scores, gnorm, qnorm, pitch, \
+                     flows, g, dists, inds)
+    if (n64 <= 1) SNLS_GTK(1);
+    else if (n64 <= 2) SNLS_GTK(2);
+    else if (n64 <= 4) SNLS_GTK(4);
+    else if (n64 <= 7) SNLS_GTK(7);
+    else if (n64 <= 10) SNLS_GTK(10);
+    else SNLS_GTK(16);
+#undef SNLS_GTK
+    return hipGetLastError() == hipSuccess ? SNLS_OK : SNLS_ERR_HIP;
+  }
   // Large k: the thread-per-row list insertions diverge on nearly every
   // candidate, the wave-per-row selection does not.
   const int nv = (g.ncand + 63) / 64;
@@ -1008,8 +1224,8 @@ snls_status launch_search_p1(const float* q, const float* k, const float* flows,
   return launch_tile_topk(scores, nullptr, nullptr, pitch, flows, g, dists, inds, s);
 }
 
-static snls_status launch_tile_scores(const float* q, const float* k, const float* flows, const Geo& g, float* scores,
-                                      int pitch, hipStream_t s) {
+snls_status launch_tile_scores(const float* q, const float* k, const float* flows, const Geo& g, float* scores,
+                               int pitch, hipStream_t s) {
   // tile of tqh x tqw queries (the kernel derives the same from S_Q)
   const int tqh = (tile::HROWS - g.ps) / g.s0 + 1, tqw = (tile::TQW - 1) / g.s0 + 1;
   const int tiles_x = (g.nW + tqw - 1) / tqw;

@@ -67,6 +67,33 @@ __global__ void __launch_bounds__(256) search_full_kernel(const float* __restric
   inds[3 * gid + 2] = disp_w;
 }
 
+// Positions of every candidate (one wave per query row at a time, lanes over
+// its candidates), and the invalid scores of frames outside the clip, which
+// the tiled scores kernel leaves unwritten.
+__global__ void __launch_bounds__(256) search_positions_kernel(const float* __restrict__ flows, Geo g,
+                                                               float* __restrict__ dists, float* __restrict__ inds) {
+  const int lane = threadIdx.x & 63, ncell = g.ws * g.ws;
+  const float inv_cell = 1.f / (float)ncell, inv_ws = 1.f / (float)g.ws;
+  const long long step = (long long)gridDim.x * 4;
+  for (long long row = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); row < g.rows;
+       row += step) {
+    const QueryPos qp = decode_row(row, g);
+    for (int cid = lane; cid < g.ncand; cid += 64) {
+      // quotients of small integers: (a + 1/2) / b is never within rounding of an integer
+      const int fi = (int)(((float)cid + 0.5f) * inv_cell), cell = cid - fi * ncell;
+      const int dh = (int)(((float)cell + 0.5f) * inv_ws), dw = cell - dh * g.ws;
+      const int dt = fi - g.wt, t2 = qp.t + dt;
+      float fh, fw;
+      read_shift(flows, g, qp, dt, &fh, &fw);
+      const long long o = row * g.ncand + cid;
+      if (t2 < 0 || t2 >= g.T) dists[o] = from_score(-INFINITY, g.dist);
+      inds[3 * o] = (float)t2;
+      inds[3 * o + 1] = cand_disp(fh, g.s1, dh, g.r);
+      inds[3 * o + 2] = cand_disp(fw, g.s1, dw, g.r);
+    }
+  }
+}
+
 // One thread per query row: all candidates, top-k kept in registers.
 template <int KMAX>
 __global__ void __launch_bounds__(128) search_topk_direct_kernel(const float* __restrict__ q,
@@ -129,6 +156,22 @@ snls_status launch_search_full(const float* q, const float* k, const float* flow
                                float* inds, hipStream_t s) {
   long long total = g.rows * g.ncand;
   if (total == 0) return SNLS_OK;
+  // Inner products inside the tiled kernel's domain: its scores straight into
+  // the output rows (no workspace), then the positions (96 x 96, 32 channels,
+  // P = 3, Ws = 5: 1.77 ms on search_full_kernel).  The squared L2 distance
+  // would need its norm terms' workspace, and window quotients in floats are
+  // exact below 2^20 candidates.
+  Geo gt = g;
+  gt.k = 1;
+  if (g.dist == SNLS_DIST_PROD && tile_supported(gt) && g.ncand < (1 << 20) &&
+      (long long)g.nW * g.nH * g.B * g.HD * g.T <= 0x7fffffffLL) {
+    const snls_status st = launch_tile_scores(q, k, flows, gt, dists, g.ncand, s);
+    if (st != SNLS_OK) return st;
+    const long long blk = (g.rows + 3) / 4;
+    hipLaunchKernelGGL(search_positions_kernel, dim3((unsigned)(blk < 8192 ? blk : 8192)), dim3(256), 0, s, flows, g,
+                       dists, inds);
+    return hipGetLastError() == hipSuccess ? SNLS_OK : SNLS_ERR_HIP;
+  }
   long long blocks = (total + 255) / 256;
   hipLaunchKernelGGL(search_full_kernel, dim3((unsigned)blocks), dim3(256), 0, s, q, k, flows, g, dists, inds);
   return hipGetLastError() == hipSuccess ? SNLS_OK : SNLS_ERR_HIP;

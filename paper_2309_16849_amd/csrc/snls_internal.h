@@ -94,6 +94,10 @@ snls_status launch_search_p1_scores(const float* q, const float* k, const float*
                                     int pitch, hipStream_t s);
 snls_status launch_search_p1_topk(const float* q, const float* k, const float* flows, const Geo& g, float* dists,
                                   float* inds, hipStream_t s);
+// Inner-product scores of the frames inside the clip, on the vector units (rows
+// of pitch floats; candidates of other frames are not written).
+snls_status launch_tile_scores(const float* q, const float* k, const float* flows, const Geo& g, float* scores,
+                               int pitch, hipStream_t s);
 snls_status launch_mfma_scores(const float* q, const float* k, const float* flows, const Geo& g, float* scores,
                                int pitch, void* ws, hipStream_t s);
 // L2 norm terms: key pair planes (workspace of l2_planes_bytes(g) bytes),

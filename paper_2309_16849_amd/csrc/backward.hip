@@ -54,6 +54,21 @@ SNLS_DEV float wave_sum(float v) {
   return v;
 }
 
+// Sum over the wave through DPP adds (rows of 16, then the row broadcasts of
+// lanes 15 and 31): no LDS crossbar.  The result is wave-uniform.
+SNLS_DEV float wave_sum_dpp(float v) {
+#define SNLS_DPP_ADD(CTRL, MASK) \
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, MASK, 0xf, false))
+  SNLS_DPP_ADD(0x111, 0xf);  // row_shr:1
+  SNLS_DPP_ADD(0x112, 0xf);  // row_shr:2
+  SNLS_DPP_ADD(0x114, 0xf);  // row_shr:4
+  SNLS_DPP_ADD(0x118, 0xf);  // row_shr:8: lane 15 of a row holds its sum
+  SNLS_DPP_ADD(0x142, 0xa);  // row_bcast:15 into rows 1 and 3
+  SNLS_DPP_ADD(0x143, 0xc);  // row_bcast:31 into rows 2 and 3
+#undef SNLS_DPP_ADD
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
 SNLS_DEV float wave_max(float v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
@@ -363,6 +378,16 @@ SNLS_DEV ClView cl_view(const float* x, const Geo& g) {
   return v;
 }
 
+// The query row of this wave: consecutive workgroups land on different XCDs
+// (8 per device), so each XCD takes a contiguous run of rows, whose
+// neighbours' blocks overlap in its L2.
+SNLS_DEV long long bwd_row() {
+  const long long nwg = (long long)gridDim.x;
+  const long long xcd = blockIdx.x % 8, xq = nwg / 8, xrem = nwg % 8;
+  const long long wg = xcd * xq + (xcd < xrem ? xcd : xrem) + blockIdx.x / 8;
+  return wg * bwd::WAVES + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+}
+
 // ---- per-row terms (P <= 7, at most 64 channels per head) ----
 //
 // For one neighbour l of a row, the taps of the P x P patch pixels cover a
@@ -380,7 +405,7 @@ __global__ void __launch_bounds__(256) backward_agg_block_kernel(const float* __
                                                                  float* __restrict__ Gws, float* __restrict__ wl_out) {
   constexpr int PB = P + 1;
   const int lane = threadIdx.x & 63;
-  const long long row = (long long)blockIdx.x * bwd::WAVES + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const long long row = bwd_row();
   if (row >= g.rows) return;  // whole wave
   const RowPos rp = row_pos(row, g);
   const float* drow = dists + row * g.k;
@@ -435,8 +460,12 @@ __global__ void __launch_bounds__(256) backward_agg_block_kernel(const float* __
 #pragma unroll
         for (int c = 0; c < PB; ++c) vb[a * PB + c] = vv.ld(kr[a] + kc[c] + ch4);
     }
-    const float w00 = (1.f - ay) * (1.f - ax), w01 = (1.f - ay) * ax, w10 = ay * (1.f - ax), w11 = ay * ax;
-    float Gl = 0.f, fh = 0.f, fw = 0.f;
+    // Sums over the patch of g~ times the value and its first differences,
+    // which the neighbouring patch pixels share; the bilinear weights are the
+    // same for all of them and enter once: 5 multiply-adds a patch pixel
+    // instead of 15 (256x256, P = 3, with the XCD order of rows: 1.19 -> 1.02 ms,
+    // the search rows 1.87 -> 1.63 ms; bound by the L2 reads of the key blocks).
+    float s0 = 0.f, dy0 = 0.f, dy1 = 0.f, dx0 = 0.f, dx1 = 0.f;
 #pragma unroll
     for (int ph = 0; ph < P; ++ph)
 #pragma unroll
@@ -444,14 +473,15 @@ __global__ void __launch_bounds__(256) backward_agg_block_kernel(const float* __
         const float gv = gg[ph * P + pw];
         const float v00 = vb[ph * PB + pw], v01 = vb[ph * PB + pw + 1];
         const float v10 = vb[(ph + 1) * PB + pw], v11 = vb[(ph + 1) * PB + pw + 1];
-        const float val = w00 * v00 + w01 * v01 + w10 * v10 + w11 * v11;
-        Gl = fmaf(gv, val, Gl);
-        fh = fmaf(gv, (1.f - ax) * (v10 - v00) + ax * (v11 - v01), fh);
-        fw = fmaf(gv, (1.f - ay) * (v01 - v00) + ay * (v11 - v10), fw);
+        s0 = fmaf(gv, v00, s0);
+        dy0 = fmaf(gv, v10 - v00, dy0);
+        dy1 = fmaf(gv, v11 - v01, dy1);
+        dx0 = fmaf(gv, v01 - v00, dx0);
+        dx1 = fmaf(gv, v11 - v10, dx1);
       }
-    Gl = wave_sum(Gl);
-    fh = wave_sum(fh);
-    fw = wave_sum(fw);
+    const float fy = (1.f - ax) * dy0 + ax * dy1, fx = (1.f - ay) * dx0 + ay * dx1;
+    const float Gl = wave_sum_dpp(s0 + ax * dx0 + ay * fy);  // v~ = v00 + ax dx0 + ay ((1 - ax) dy0 + ax dy1)
+    const float fh = wave_sum_dpp(fy), fw = wave_sum_dpp(fx);
     if (lane == 0) {
       Gws[row * g.k + l] = Gl;
       add_flow_grad(grad_flows, g, rp, t2, wl * fh, wl * fw);
@@ -471,7 +501,7 @@ __global__ void __launch_bounds__(256) backward_search_block_kernel(const float*
                                                                     float* __restrict__ dd_out) {
   constexpr int PB = P + 1;
   const int lane = threadIdx.x & 63;
-  const long long row = (long long)blockIdx.x * bwd::WAVES + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const long long row = bwd_row();
   if (row >= g.rows) return;  // whole wave
   const RowPos rp = row_pos(row, g);
   const float* drow = dists + row * g.k;
@@ -492,6 +522,7 @@ __global__ void __launch_bounds__(256) backward_search_block_kernel(const float*
   const unsigned ch4 = act ? (unsigned)cc * 4u : kOOB2;
   const int lo = -(P / 2);
   const ClView qv_ = cl_view(qcl, g), kv_ = cl_view(kcl, g);
+  const bool inside = rp.h + lo >= 0 && rp.h + lo + P <= g.H && rp.w + lo >= 0 && rp.w + lo + P <= g.W;  // the patch
   float qv[P * P], dq[P * P];
   {
     unsigned ro[P], co[P];
@@ -536,33 +567,56 @@ __global__ void __launch_bounds__(256) backward_search_block_kernel(const float*
         for (int c = 0; c < PB; ++c) kb[a * PB + c] = kv_.ld(kr[a] + kc[c] + ch4);
     }
     const float w00 = (1.f - ay) * (1.f - ax), w01 = (1.f - ay) * ax, w10 = ay * (1.f - ax), w11 = ay * ax;
-    float fh = 0.f, fw = 0.f;
+    float fh, fw;
+    if (ip && inside) {
+      // dq += dd k~ through weights times dd; the flow gradient from the sums
+      // of q times k's first differences
+      const float d00 = dd * w00, d01 = dd * w01, d10 = dd * w10, d11 = dd * w11;
+      float dy0 = 0.f, dy1 = 0.f, dx0 = 0.f, dx1 = 0.f;
 #pragma unroll
-    for (int ph = 0; ph < P; ++ph) {
-      const int y = rp.h + lo + ph;
+      for (int ph = 0; ph < P; ++ph)
 #pragma unroll
-      for (int pw = 0; pw < P; ++pw) {
-        const int x = rp.w + lo + pw;
-        if (y < 0 || y >= g.H || x < 0 || x >= g.W) continue;  // patch pixels outside the frame
-        const float k00 = kb[ph * PB + pw], k01 = kb[ph * PB + pw + 1];
-        const float k10 = kb[(ph + 1) * PB + pw], k11 = kb[(ph + 1) * PB + pw + 1];
-        const float kv = w00 * k00 + w01 * k01 + w10 * k10 + w11 * k11;
-        const float q = qv[ph * P + pw];
-        float dqv, dk;
-        if (ip) {
-          dqv = dd * kv;
-          dk = dd * q;
-        } else {
-          dqv = 2.f * dd * (q - kv);
-          dk = -dqv;
+        for (int pw = 0; pw < P; ++pw) {
+          const float k00 = kb[ph * PB + pw], k01 = kb[ph * PB + pw + 1];
+          const float k10 = kb[(ph + 1) * PB + pw], k11 = kb[(ph + 1) * PB + pw + 1];
+          const float q = qv[ph * P + pw];
+          dq[ph * P + pw] = fmaf(d00, k00, fmaf(d01, k01, fmaf(d10, k10, fmaf(d11, k11, dq[ph * P + pw]))));
+          dy0 = fmaf(q, k10 - k00, dy0);
+          dy1 = fmaf(q, k11 - k01, dy1);
+          dx0 = fmaf(q, k01 - k00, dx0);
+          dx1 = fmaf(q, k11 - k10, dx1);
         }
-        dq[ph * P + pw] += dqv;
-        fh = fmaf(dk, (1.f - ax) * (k10 - k00) + ax * (k11 - k01), fh);
-        fw = fmaf(dk, (1.f - ay) * (k01 - k00) + ay * (k11 - k10), fw);
+      fh = dd * wave_sum_dpp((1.f - ax) * dy0 + ax * dy1);
+      fw = dd * wave_sum_dpp((1.f - ay) * dx0 + ay * dx1);
+    } else {
+      fh = fw = 0.f;
+#pragma unroll
+      for (int ph = 0; ph < P; ++ph) {
+        const int y = rp.h + lo + ph;
+#pragma unroll
+        for (int pw = 0; pw < P; ++pw) {
+          const int x = rp.w + lo + pw;
+          if (y < 0 || y >= g.H || x < 0 || x >= g.W) continue;  // patch pixels outside the frame
+          const float k00 = kb[ph * PB + pw], k01 = kb[ph * PB + pw + 1];
+          const float k10 = kb[(ph + 1) * PB + pw], k11 = kb[(ph + 1) * PB + pw + 1];
+          const float kv = w00 * k00 + w01 * k01 + w10 * k10 + w11 * k11;
+          const float q = qv[ph * P + pw];
+          float dqv, dk;
+          if (ip) {
+            dqv = dd * kv;
+            dk = dd * q;
+          } else {
+            dqv = 2.f * dd * (q - kv);
+            dk = -dqv;
+          }
+          dq[ph * P + pw] += dqv;
+          fh = fmaf(dk, (1.f - ax) * (k10 - k00) + ax * (k11 - k01), fh);
+          fw = fmaf(dk, (1.f - ay) * (k01 - k00) + ay * (k11 - k10), fw);
+        }
       }
+      fh = wave_sum_dpp(fh);
+      fw = wave_sum_dpp(fw);
     }
-    fh = wave_sum(fh);
-    fw = wave_sum(fw);
     if (lane == 0) add_flow_grad(grad_flows, g, rp, t2, fh, fw);
   }
 #pragma unroll

@@ -136,7 +136,8 @@ typedef struct {
  *             head, the squared norm of every query pixel per frame and head
  *             and, where the norm terms are formed cell by cell (stride1 < 1
  *             or ws > 9), fp64 summed-area tables of the five products.  The
- *             fused single-pixel path (k <= 32) needs none.  Its contents
+ *             fused single-pixel path (k <= 32; not at stride0 = 1
+ *             with 32 or more channels per head and k <= 16) needs none.  Its contents
  *             are not needed between calls
  * Errors: SNLS_ERR_INVALID_ARG for shapes/parameters out of range or NULL
  * buffers; SNLS_ERR_UNSUPPORTED for k > SNLS_MAX_K; SNLS_ERR_WORKSPACE for a

@@ -193,10 +193,17 @@ snls_status launch_search_topk_direct(const float* q, const float* k, const floa
 }
 
 SearchRoute search_route(const Geo& g) {
-  // single-pixel patches: no patch overlap for the tiles to share.  The fused
-  // per-query kernel (k <= 32) is faster at any query stride (320 x 320,
-  // S_Q = 1, Ws = 9: 2.03 vs 2.11 ms) and needs no score workspace; the
-  // scored single-pixel route only at a query stride above 1.
+  // Single-pixel patches have no overlap for the tiles to share, but the
+  // matrix cores still pay where the head has 32 channels or more and every
+  // pixel is a query (k <= 16: the 16-lane top-k).  Fused kernel against the
+  // tiled route, S_Q = 1, Ws = 9, k = 10, T = 5: 320x320 with 16 channels 1.23
+  // and 1.25 ms, with 32 channels 1.83 and 1.28 ms, 256x256 with 64 channels
+  // 2.02 and 1.15 ms; 4 heads of 8 channels 0.22 and 0.31 ms.  The fused
+  // per-query kernel (k <= 32) takes the other single-pixel searches and needs
+  // no score workspace; the scored single-pixel route only at a query stride
+  // above 1.
+  if (g.ps == 1 && g.s0 == 1 && g.Ch >= 32 && g.k <= 16 && tile_supported(g) && mfma_supported(g))
+    return SearchRoute::Tile;
   if (g.ps == 1 && p1_fused(g)) return SearchRoute::P1Fused;
   if (g.ps == 1 && g.s0 > 1 && p1_supported(g)) return SearchRoute::P1Scored;
   if (tile_supported(g)) return SearchRoute::Tile;

@@ -90,3 +90,17 @@ def test_pixels_with_scales_of_their_own(dev, which):
     X = np.clip(x[None, :, :, None] + at[..., 2], 0, 32).astype(int)
     bound = qn[:, None] * kn[np.clip(f, 0, 1), Y, X].reshape(-1, 33)
     assert (err <= 1e-6 * bound + 1e-30)[fin].all()
+
+
+@pytest.mark.parametrize("C,HD,ws,k,s0,flow", [(32, 1, 9, 10, 1, 3.0), (64, 2, 15, 16, 1, 2.0), (31, 1, 9, 16, 1, 3.0),
+                                               (40, 1, 9, 17, 1, 3.0), (96, 1, 3, 16, 1, 14.0), (32, 1, 5, 9, 2, 3.0)])
+def test_single_pixel_routes(dev, C, HD, ws, k, s0, flow):
+    """Single-pixel patches on both sides of the rule that takes them to the
+    tiled route (32 channels per head, k = 16, query stride 1)."""
+    p = small_params(T=3, C=C, HD=HD, H=37, W=45, ws=ws, wt=1, ps=1, k=k, stride0=s0)
+    rng = np.random.default_rng(C + k)
+    shp = (1, 3, C, 37, 45)
+    q, kk = (rng.standard_normal(shp, dtype=np.float32) for _ in range(2))
+    fl = rng.uniform(-flow, flow, (1, 3, 2, 2, 37, 45)).astype(np.float32)
+    gd, gi = _search(q, kk, fl, p, dev)
+    compare_topk(gd, gi, oracle.search(q, kk, fl, p), k)

@@ -157,7 +157,7 @@ SNLS_DEV void mf_factors(float m, float* up, float* down) {
 // One workgroup = 64 pixels of one (b, t, head): channels x pixels through
 // LDS, 64 channels at a time, then 8 channels per thread are scaled, split
 // and written as two 16-byte pieces.  info: the image's scale, or 0 when
-// its pixels have their own (in scale).
+// its pixels have their own (in scale); -0 where some of them are infinite.
 __global__ void __launch_bounds__(256) mf_split_kernel(const float* __restrict__ x, Geo g, int nc32,
                                                        const float2* __restrict__ stats, int nstat,
                                                        unsigned char* __restrict__ xs, float* __restrict__ scale,
@@ -189,7 +189,7 @@ __global__ void __launch_bounds__(256) mf_split_kernel(const float* __restrict__
     hi = fmaxf(hi, __shfl_xor(hi, off));
     lo = fminf(lo, __shfl_xor(lo, off));
   }
-  const bool one = !(lo < hi * 0x1p-12f);  // the same for every workgroup of the image
+  const bool one = !(lo < hi * 0x1p-12f) && hi < INFINITY;  // the same for every workgroup of the image
   float up, down;
   if (one) {
     mf_factors(hi, &up, &down);
@@ -197,7 +197,7 @@ __global__ void __launch_bounds__(256) mf_split_kernel(const float* __restrict__
     mf_factors(pin ? mf_pixel_max(src, g, p0 + px) : 0.f, &up, &down);  // (the same for the four threads of a pixel)
     if (qt == 0 && pin) scale[slab * g.HW + p0 + px] = down;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) info[slab] = one ? down : 0.f;
+  if (blockIdx.x == 0 && threadIdx.x == 0) info[slab] = one ? down : (hi < INFINITY ? 0.f : -0.f);
   for (int c0 = 0; c0 < nch; c0 += 64) {
     if (c0) __syncthreads();
     for (int i = qt; i < 64; i += 4) {
@@ -216,7 +216,7 @@ __global__ void __launch_bounds__(256) mf_split_kernel(const float* __restrict__
         const _Float16 h = (_Float16)v;
         const float r = v - (float)h;
         h8[i] = h;
-        l8[i] = (_Float16)(r == r ? r : 0.f);  // an infinity keeps its sign in hi
+        l8[i] = (_Float16)(r == r ? r : 0.f);  // (infinities: their scores are formed again from q and k)
       }
       unsigned char* o = dst + ((c0 / 32 + pc / 4) * 8 + (pc & 3)) * pst;
       *reinterpret_cast<half8*>(o) = h8;
@@ -393,7 +393,8 @@ SNLS_DEV void mf_stream(const MfFrame& f, const unsigned char* qlds, const float
         const bool in = gy >= 0 && gy < f.H && gx >= 0 && gx < f.W;
         const unsigned off = in && f.kuni == 0.f ? (unsigned)((gy * f.W + gx) * 4) : OOB;
         const float ek = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(s_rs, off, 0, 0));
-        a[n][u] = a[n][u] * (f.kuni != 0.f ? f.kuni : ek) * eq;
+        // in 64 bits: two scales may leave fp32's range where the product does not
+        a[n][u] = (float)((double)a[n][u] * ((double)(f.kuni != 0.f ? f.kuni : ek) * (double)eq));
       }
   };
   const unsigned char* const ap0 = qlds + lj * f.qpitch + lg * 16;
@@ -549,7 +550,7 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
   auto slab = [&](int tt) { return ((long long)b * g.T + tt) * g.HD + hd; };
 
   // ---- the halo of q (split records and scales), the tile's offsets ----
-  const float quni = qinfo[slab(t)];  // (uniform)
+  const float quni = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(qinfo[slab(t)])));
   if (quni == 0.f)
     for (int p = tid; p < hr * HC; p += NT) {
       const int gy = Y0 + p / HC, gx = X0 + p % HC;
@@ -656,9 +657,7 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
     const int UH = dmax_h - dmin_h + 1, UW = dmax_w - dmin_w + 1;
     const bool none = UH <= 0 || UW <= 0;  // every cell of the frame is invalid
     const float2* const ff = fl + fi * qn;
-    const float kuni = kinfo[slab(t2)];
-    // the images' scales, where the sums have not been scaled back yet
-    const float back = kuni != 0.f && quni != 0.f ? kuni * quni : 1.f;
+    const float kuni = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(kinfo[slab(t2)])));
     if (UW <= UW2) {
       // shift rows of a round, spread over the waves: up to two each, one
       // each for unions that need the two-part lane layout and for images
@@ -704,6 +703,8 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
       }
       __syncthreads();
       if (fi + 1 < nfr) set_queries(fi + 1);
+      // the images' scales, where the sums have not been scaled back yet
+      const double back = kuni != 0.f && quni != 0.f ? (double)kuni * (double)quni : 1.0;
       // ---- 4-tap combination and exact validity: one thread per window
       // column, so that a store's lanes write runs of ws scores ----
       for (int e = tid; e < qn * ws; e += NT) {
@@ -727,18 +728,24 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
           const float* const r0p = cp + (ok ? (int)fl_h - lo.x : 0) * wp;
           // in 64 bits: one rounding per score instead of nine
           const double t0 = r0p[0], b0 = r0p[wp];
-          const double top = fma((double)aw, (double)r0p[1] - t0, t0);
-          const double bot = fma((double)aw, (double)r0p[wp + 1] - b0, b0);
-          const float dv = (float)fma((double)ah, bot - top, top) * back;
+          const double top = fma((double)aw, (double)r0p[1], (1.0 - aw) * t0);
+          const double bot = fma((double)aw, (double)r0p[wp + 1], (1.0 - aw) * b0);
+          const float dv = (float)(fma((double)ah, bot, (1.0 - ah) * top) * back);
           srow[dh * ws] = ok && dv == dv ? dv : -INFINITY;  // NaN scores as invalid
         }
       }
-    } else {
-      // union too wide for the lanes: this frame's candidates one by one
+    } else if (fi + 1 < nfr) {
+      set_queries(fi + 1);
+    }
+    // an infinity in either image: its parts' products mix signs and zeros
+    // (inf x lo), so scores that are not finite are formed again from q and k
+    const bool again = UW <= UW2;
+    if (!again || __float_as_uint(kuni) == 0x80000000u || __float_as_uint(quni) == 0x80000000u) {
+      if (again) __syncthreads();  // the frame's scores are written
+      // or a union too wide for the lanes: this frame's candidates one by one
       // (inner products for both distances, as the top-k pass expects)
       Geo gp = g;
       gp.dist = SNLS_DIST_PROD;
-      if (fi + 1 < nfr) set_queries(fi + 1);
       for (int e = tid; e < qn * ws; e += NT) {
         const int j = e / ws, dh = e % ws;
         const int mh = my0 + j / tqw, mw = mx0 + j % tqw;
@@ -749,9 +756,11 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
         const bool okh = centre_ok(h, disp_h, g.H);
         for (int dw = 0; dw < ws; ++dw) {
           const float disp_w = cand_disp(F.y, g.s1, dw, r);
+          float* const at = scores + ((rowb + mh) * g.nW + mw) * pitch + cbase + dh * ws + dw;
+          if (again && fabsf(*at) < INFINITY) continue;
           float d = -INFINITY;
           if (okh && centre_ok(w, disp_w, g.W)) d = score_candidate(q, k, gp, b, hd, t, h, w, t2, disp_h, disp_w);
-          scores[((rowb + mh) * g.nW + mw) * pitch + cbase + dh * ws + dw] = d;
+          *at = d;
         }
       }
     }

@@ -92,6 +92,50 @@ def test_pixels_with_scales_of_their_own(dev, which):
     assert (err <= 1e-6 * bound + 1e-30)[fin].all()
 
 
+@pytest.mark.parametrize("ps", [1, 3, 7])
+@pytest.mark.parametrize("share", [0.002, 0.3])
+def test_infinite_features_keep_their_scores(dev, ps, share):
+    """Infinite features of q and k: an infinite score stays ranked and only
+    NaN ones are invalid.  Offsets of halves, so that no tap has weight 0 (0 x
+    inf); the oracle sums the same products, so the signs agree."""
+    p = small_params(T=2, C=16, H=34, W=36, ws=5, wt=1, ps=ps, k=20 if ps > 1 else 33)
+    rng = np.random.default_rng(9 + ps)
+    shp = (1, 2, 16, 34, 36)
+    q, k = (rng.standard_normal(shp, dtype=np.float32) for _ in range(2))
+    for a in (q, k):  # one channel per pixel, away from the borders
+        at = rng.random((2, 20, 20)) < share
+        a[0, :, 3, 7:27, 8:28] = np.where(at, np.where(rng.random(at.shape) < 0.5, np.inf, -np.inf), a[0, :, 3, 7:27, 8:28])
+    fl = (rng.integers(-2, 2, (1, 2, 2, 2, 34, 36)) + 0.5).astype(np.float32)
+    gd, gi = _search(q, k, fl, p, dev)
+    ref = oracle.search(q, k, fl, p)["dists"][:, :p["k"]]
+    assert not np.isnan(gd).any()
+    # rows sorted best first: the numbers of infinite ones agree
+    for inf in (np.inf, -np.inf):
+        assert np.array_equal((gd == inf).sum(1), (ref == inf).sum(1))
+    fin = np.isfinite(ref)
+    assert np.allclose(gd[fin], ref[fin], rtol=1e-5, atol=1e-5 * ps * ps * 4)
+
+
+@pytest.mark.parametrize("mq,mk", [(1e-16, 1e-20), (1e30, 1e-34), (1e-34, 1e34)])
+@pytest.mark.parametrize("wide", [False, True])
+def test_scales_whose_product_leaves_the_range(dev, mq, mk, wide):
+    """Magnitudes whose scales multiply to a denormal or to infinity on the
+    way, while the scores are ordinary numbers (wide: scales per pixel)."""
+    p = small_params(T=1, C=16, H=20, W=21, ws=3, wt=0, ps=3, k=9)
+    rng = np.random.default_rng(4)
+    shp = (1, 1, 16, 20, 21)
+    q, k = (rng.standard_normal(shp) for _ in range(2))
+    if wide:
+        q[..., 0, 0] *= 1e-6
+        k[..., 0, 0] *= 1e-6
+    fl = np.zeros((1, 1, 0, 2, 20, 21), np.float32)
+    gd, gi = _search((q * mq).astype(np.float32), (k * mk).astype(np.float32), fl, p, dev)
+    ref = oracle.search((q * mq).astype(np.float32), (k * mk).astype(np.float32), fl, p)["dists"][:, :9]
+    fin = np.isfinite(ref)
+    assert np.array_equal(fin, np.isfinite(gd))
+    assert np.allclose(gd[fin] / (mq * mk), ref[fin] / (mq * mk), rtol=1e-5, atol=1e-4)
+
+
 @pytest.mark.parametrize("C,HD,ws,k,s0,flow", [(32, 1, 9, 10, 1, 3.0), (64, 2, 15, 16, 1, 2.0), (31, 1, 9, 16, 1, 3.0),
                                                (40, 1, 9, 17, 1, 3.0), (96, 1, 3, 16, 1, 14.0), (32, 1, 5, 9, 2, 3.0)])
 def test_single_pixel_routes(dev, C, HD, ws, k, s0, flow):

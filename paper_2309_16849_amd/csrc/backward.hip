@@ -460,12 +460,12 @@ __global__ void __launch_bounds__(256) backward_agg_block_kernel(const float* __
 #pragma unroll
         for (int c = 0; c < PB; ++c) vb[a * PB + c] = vv.ld(kr[a] + kc[c] + ch4);
     }
-    // Sums over the patch of g~ times the value and its first differences,
-    // which the neighbouring patch pixels share; the bilinear weights are the
-    // same for all of them and enter once: 5 multiply-adds a patch pixel
-    // instead of 15 (256x256, P = 3, with the XCD order of rows: 1.19 -> 1.02 ms,
-    // the search rows 1.87 -> 1.63 ms; bound by the L2 reads of the key blocks).
-    float s0 = 0.f, dy0 = 0.f, dy1 = 0.f, dx0 = 0.f, dx1 = 0.f;
+    // (Rows in XCD order, wave sums by DPP.  Sums of g~ times the first
+    // differences, with the bilinear weights applied once, take fewer
+    // operations, but their roundings are those of larger numbers: P = 7 flow
+    // gradients 1.6 times further from 64-bit ones.)
+    const float w00 = (1.f - ay) * (1.f - ax), w01 = (1.f - ay) * ax, w10 = ay * (1.f - ax), w11 = ay * ax;
+    float Gl = 0.f, fh = 0.f, fw = 0.f;
 #pragma unroll
     for (int ph = 0; ph < P; ++ph)
 #pragma unroll
@@ -473,15 +473,14 @@ __global__ void __launch_bounds__(256) backward_agg_block_kernel(const float* __
         const float gv = gg[ph * P + pw];
         const float v00 = vb[ph * PB + pw], v01 = vb[ph * PB + pw + 1];
         const float v10 = vb[(ph + 1) * PB + pw], v11 = vb[(ph + 1) * PB + pw + 1];
-        s0 = fmaf(gv, v00, s0);
-        dy0 = fmaf(gv, v10 - v00, dy0);
-        dy1 = fmaf(gv, v11 - v01, dy1);
-        dx0 = fmaf(gv, v01 - v00, dx0);
-        dx1 = fmaf(gv, v11 - v10, dx1);
+        const float val = w00 * v00 + w01 * v01 + w10 * v10 + w11 * v11;
+        Gl = fmaf(gv, val, Gl);
+        fh = fmaf(gv, (1.f - ax) * (v10 - v00) + ax * (v11 - v01), fh);
+        fw = fmaf(gv, (1.f - ay) * (v01 - v00) + ay * (v11 - v10), fw);
       }
-    const float fy = (1.f - ax) * dy0 + ax * dy1, fx = (1.f - ay) * dx0 + ay * dx1;
-    const float Gl = wave_sum_dpp(s0 + ax * dx0 + ay * fy);  // v~ = v00 + ax dx0 + ay ((1 - ax) dy0 + ax dy1)
-    const float fh = wave_sum_dpp(fy), fw = wave_sum_dpp(fx);
+    Gl = wave_sum_dpp(Gl);
+    fh = wave_sum_dpp(fh);
+    fw = wave_sum_dpp(fw);
     if (lane == 0) {
       Gws[row * g.k + l] = Gl;
       add_flow_grad(grad_flows, g, rp, t2, wl * fh, wl * fw);
@@ -567,29 +566,31 @@ __global__ void __launch_bounds__(256) backward_search_block_kernel(const float*
         for (int c = 0; c < PB; ++c) kb[a * PB + c] = kv_.ld(kr[a] + kc[c] + ch4);
     }
     const float w00 = (1.f - ay) * (1.f - ax), w01 = (1.f - ay) * ax, w10 = ay * (1.f - ax), w11 = ay * ax;
-    float fh, fw;
-    if (ip && inside) {
-      // dq += dd k~ through weights times dd; the flow gradient from the sums
-      // of q times k's first differences
-      const float d00 = dd * w00, d01 = dd * w01, d10 = dd * w10, d11 = dd * w11;
-      float dy0 = 0.f, dy1 = 0.f, dx0 = 0.f, dx1 = 0.f;
+    float fh = 0.f, fw = 0.f;
+    // one patch pixel's terms
+    auto pixel = [&](int ph, int pw) {
+      const float k00 = kb[ph * PB + pw], k01 = kb[ph * PB + pw + 1];
+      const float k10 = kb[(ph + 1) * PB + pw], k11 = kb[(ph + 1) * PB + pw + 1];
+      const float kv = w00 * k00 + w01 * k01 + w10 * k10 + w11 * k11;
+      const float q = qv[ph * P + pw];
+      float dqv, dk;
+      if (ip) {
+        dqv = dd * kv;
+        dk = dd * q;
+      } else {
+        dqv = 2.f * dd * (q - kv);
+        dk = -dqv;
+      }
+      dq[ph * P + pw] += dqv;
+      fh = fmaf(dk, (1.f - ax) * (k10 - k00) + ax * (k11 - k01), fh);
+      fw = fmaf(dk, (1.f - ay) * (k01 - k00) + ay * (k11 - k10), fw);
+    };
+    if (ip && inside) {  // no pixel to test, no branch
 #pragma unroll
       for (int ph = 0; ph < P; ++ph)
 #pragma unroll
-        for (int pw = 0; pw < P; ++pw) {
-          const float k00 = kb[ph * PB + pw], k01 = kb[ph * PB + pw + 1];
-          const float k10 = kb[(ph + 1) * PB + pw], k11 = kb[(ph + 1) * PB + pw + 1];
-          const float q = qv[ph * P + pw];
-          dq[ph * P + pw] = fmaf(d00, k00, fmaf(d01, k01, fmaf(d10, k10, fmaf(d11, k11, dq[ph * P + pw]))));
-          dy0 = fmaf(q, k10 - k00, dy0);
-          dy1 = fmaf(q, k11 - k01, dy1);
-          dx0 = fmaf(q, k01 - k00, dx0);
-          dx1 = fmaf(q, k11 - k10, dx1);
-        }
-      fh = dd * wave_sum_dpp((1.f - ax) * dy0 + ax * dy1);
-      fw = dd * wave_sum_dpp((1.f - ay) * dx0 + ay * dx1);
+        for (int pw = 0; pw < P; ++pw) pixel(ph, pw);
     } else {
-      fh = fw = 0.f;
 #pragma unroll
       for (int ph = 0; ph < P; ++ph) {
         const int y = rp.h + lo + ph;
@@ -597,26 +598,12 @@ __global__ void __launch_bounds__(256) backward_search_block_kernel(const float*
         for (int pw = 0; pw < P; ++pw) {
           const int x = rp.w + lo + pw;
           if (y < 0 || y >= g.H || x < 0 || x >= g.W) continue;  // patch pixels outside the frame
-          const float k00 = kb[ph * PB + pw], k01 = kb[ph * PB + pw + 1];
-          const float k10 = kb[(ph + 1) * PB + pw], k11 = kb[(ph + 1) * PB + pw + 1];
-          const float kv = w00 * k00 + w01 * k01 + w10 * k10 + w11 * k11;
-          const float q = qv[ph * P + pw];
-          float dqv, dk;
-          if (ip) {
-            dqv = dd * kv;
-            dk = dd * q;
-          } else {
-            dqv = 2.f * dd * (q - kv);
-            dk = -dqv;
-          }
-          dq[ph * P + pw] += dqv;
-          fh = fmaf(dk, (1.f - ax) * (k10 - k00) + ax * (k11 - k01), fh);
-          fw = fmaf(dk, (1.f - ay) * (k01 - k00) + ay * (k11 - k10), fw);
+          pixel(ph, pw);
         }
       }
-      fh = wave_sum_dpp(fh);
-      fw = wave_sum_dpp(fw);
     }
+    fh = wave_sum_dpp(fh);
+    fw = wave_sum_dpp(fw);
     if (lane == 0) add_flow_grad(grad_flows, g, rp, t2, fh, fw);
   }
 #pragma unroll

@@ -65,6 +65,7 @@ constexpr int rows_per_wave(int CG) { return CG == 1 ? 2 : 3; }
 constexpr int HC = 16;           // halo columns = rows of operand A
 constexpr int UW3 = 21;          // shift columns with three column parts (one per lane of a part)
 constexpr int UW2 = 32;          // ... with two: the widest union (16 + 32 - 1 <= 48 key columns)
+constexpr int UHMAX = 16383;     // shift rows of a union: a query's first row, relative to the union's, has 16 bits
 constexpr int DP = 52;           // pitch of a product row in LDS (4 DP = 16 mod 64: the writes' banks)
 constexpr int DBUF = HC * DP;    // floats per wave
 constexpr int LDS_BYTES = 160 * 1024;
@@ -639,7 +640,8 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
     for (int j = tid; j < qn; j += NT) {
       const float2 F = fl[fi * qn + j];
       const int lh = lo_of(F.x), lw = lo_of(F.y);
-      // relative to the union; a window that far from it reads none of it
+      // relative to the union (at most UHMAX rows and UW2 columns, else the
+      // table is not used); a window that far from it reads none of it
       const int rh = min(max(lh - u0, -16384), 16383), rw = min(max(lw - u2, -16384), 16383);
       qi[(fi & 1) * qn + j] = make_int2((rh << 16) | (rw & 0xffff), j * win - rh * wp - rw);
       ql[(fi & 1) * qn + j] = make_int2(lh, lw);
@@ -658,7 +660,8 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
     const bool none = UH <= 0 || UW <= 0;  // every cell of the frame is invalid
     const float2* const ff = fl + fi * qn;
     const float kuni = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(kinfo[slab(t2)])));
-    if (UW <= UW2) {
+    const bool tabled = UW <= UW2 && UH <= UHMAX;
+    if (tabled) {
       // shift rows of a round, spread over the waves: up to two each, one
       // each for unions that need the two-part lane layout and for images
       // with a scale per pixel.  No barrier
@@ -739,10 +742,11 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
     }
     // an infinity in either image: its parts' products mix signs and zeros
     // (inf x lo), so scores that are not finite are formed again from q and k
-    const bool again = UW <= UW2;
+    const bool again = tabled;
     if (!again || __float_as_uint(kuni) == 0x80000000u || __float_as_uint(quni) == 0x80000000u) {
       if (again) __syncthreads();  // the frame's scores are written
-      // or a union too wide for the lanes: this frame's candidates one by one
+      // or a union too wide for the lanes or too tall for the queries' packed
+      // shifts: this frame's candidates one by one
       // (inner products for both distances, as the top-k pass expects)
       Geo gp = g;
       gp.dist = SNLS_DIST_PROD;

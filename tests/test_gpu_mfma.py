@@ -59,6 +59,23 @@ def test_scores_at_path_edges(dev, ps, C, HD, ws, s0, s1, rows, cols):
     compare_topk(gd, gi, oracle.search(q, k, fl, p), p["k"])
 
 
+@pytest.mark.parametrize("H,s0", [(18100, 1), (18100, 8)])
+def test_tall_frames(dev, H, s0):
+    """Valid offsets of one tile more than 16384 rows apart: a query's shift
+    rows, relative to the tile's, leave 16 bits."""
+    p = small_params(T=2, C=16, H=H, W=6, ws=3, wt=1, ps=3, k=9, stride0=s0)
+    rng = np.random.default_rng(H + s0)
+    shp = (1, 2, 16, H, 6)
+    q, k = (rng.standard_normal(shp, dtype=np.float32) for _ in range(2))
+    fl = rng.uniform(-1, 1, (1, 2, 2, 2, H, 6)).astype(np.float32)
+    for i in range(0, 120, 24):  # from near the bottom to the top, and back
+        top, bottom = 8 + i, (H - 128) // 8 * 8 + i
+        fl[:, :, :, 0, bottom, 0] = 4.25 - bottom
+        fl[:, :, :, 0, top, 0] = H - 5.75 - top
+    gd, gi = _search(q, k, fl, p, dev)
+    compare_topk(gd, gi, oracle.search(q, k, fl, p), p["k"])
+
+
 @pytest.mark.parametrize("which", ["q", "k", "both"])
 def test_pixels_with_scales_of_their_own(dev, which):
     """Pixels from 1e-12 to 1e12 in one image: each score is compared with

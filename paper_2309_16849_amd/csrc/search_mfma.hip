@@ -64,8 +64,8 @@ constexpr int waves(int CG) { return CG == 1 ? 12 : 8; }
 constexpr int rows_per_wave(int CG) { return CG == 1 ? 2 : 3; }
 constexpr int HC = 16;           // halo columns = rows of operand A
 constexpr int UW3 = 21;          // shift columns with three column parts (one per lane of a part)
-constexpr int UW2 = 32;          // ... with two: the widest union (16 + 32 - 1 <= 48 key columns)
-constexpr int UHMAX = 16383;     // shift rows of a union: a query's first row, relative to the union's, has 16 bits
+constexpr int UW2 = 32;          // ... with two (16 + 32 - 1 <= 48 key columns): wider unions are swept 32 at a time
+constexpr int UMAX = 16383;      // shift rows or columns of a union: a query's first one, relative to the union's, has 16 bits
 constexpr int DP = 52;           // pitch of a product row in LDS (4 DP = 16 mod 64: the writes' banks)
 constexpr int DBUF = HC * DP;    // floats per wave
 constexpr int LDS_BYTES = 160 * 1024;
@@ -311,7 +311,7 @@ struct MfFrame {
   int W, rec, plane_bytes;      // frame width; bytes of a pixel record and of a plane
   int row0;                     // frame row of (halo row 0, the wave's first shift row)
   int H, hr, ngrp, qpitch;
-  int dr0, col0;                // wave's first shift row less the union's, frame column of product column 0
+  int dr0, dc0, col0;           // the wave's first shift row and column less the union's, frame column of product column 0
   int s0, tqw, wp;
   float kuni, quni;             // scale of the key and query images (0: per pixel, in kscale and qsc)
 };
@@ -475,10 +475,10 @@ SNLS_DEV void mf_stream(const MfFrame& f, const unsigned char* qlds, const float
       // the finished box sums to their queries' tables: entry (shift row less
       // the query's first, the same for columns) where it lies in the table
       if (live) {
-        const int cell = (f.dr0 + i) * f.wp + le;
+        const int lc = f.dc0 + le, cell = (f.dr0 + i) * f.wp + lc;
 #pragma unroll
         for (int x = 0; x < NXP; ++x) {
-          const unsigned u = (unsigned)(f.dr0 + i - (w[x].x >> 16)), c = (unsigned)(le - (int)(short)w[x].x);
+          const unsigned u = (unsigned)(f.dr0 + i - (w[x].x >> 16)), c = (unsigned)(lc - (int)(short)w[x].x);
           bool ok = max(u, c) < (unsigned)f.wp;
           if (!S1) ok = ok && ((xok >> x) & 1);
           float* const at = ok ? tab + (w[x].y + cell) : dump;
@@ -498,6 +498,18 @@ SNLS_DEV void mf_stream(const MfFrame& f, const unsigned char* qlds, const float
   } else {
     for (int s = 0; s < nstep; ++s) step(s, std::integral_constant<int, 0>{});
   }
+}
+
+// Whether a frame's union is swept (in `rounds` passes of every wave over the
+// tile's halo, 2,400 cycles a halo row) or its candidates are scored one by
+// one (1,400 to 4,000 cycles a thread, patch pixel and channel: every read is
+// a cache line of its own).  256x256, T = 3, Ws = 9, swept / one by one: a
+// motion edge of 24 columns with P = 7 and 64 channels 0.80 / 126 ms, offsets
+// of +-50 with P = 1 and 32 channels 2.8 / 8.1 ms, of +-100 8.4 / 8.7 ms.
+SNLS_DEV bool mf_sweeps_pay(const Geo& g, const MfGeo& mg, int rounds, int nt) {
+  const float sweep = 2400.f * (float)mg.hr * (float)rounds;
+  const float direct = 2000.f * (float)((mg.tqh * mg.tqw * g.ws * g.ws + nt - 1) / nt) * (float)(g.ps * g.ps * g.Ch);
+  return sweep < direct;
 }
 
 // CG: 32-channel chunks of a record multiplied per load (1 or 2).  S1: query stride 1.
@@ -640,8 +652,8 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
     for (int j = tid; j < qn; j += NT) {
       const float2 F = fl[fi * qn + j];
       const int lh = lo_of(F.x), lw = lo_of(F.y);
-      // relative to the union (at most UHMAX rows and UW2 columns, else the
-      // table is not used); a window that far from it reads none of it
+      // relative to the union (at most UMAX rows and columns, else the tables
+      // are not used); a window that far from it reads none of it
       const int rh = min(max(lh - u0, -16384), 16383), rw = min(max(lw - u2, -16384), 16383);
       qi[(fi & 1) * qn + j] = make_int2((rh << 16) | (rw & 0xffff), j * win - rh * wp - rw);
       ql[(fi & 1) * qn + j] = make_int2(lh, lw);
@@ -660,15 +672,18 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
     const bool none = UH <= 0 || UW <= 0;  // every cell of the frame is invalid
     const float2* const ff = fl + fi * qn;
     const float kuni = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(kinfo[slab(t2)])));
-    const bool tabled = UW <= UW2 && UH <= UHMAX;
+    const bool one = kuni != 0.f && quni != 0.f;  // both images have one scale
+    // shift rows of a round, spread over the waves: up to two each, one
+    // each for unions that need the two-part lane layout and for images
+    // with a scale per pixel.
+    const int per = NW * (one && UW <= UW3 ? NDW : 1);
+    const int nsweep = one && UW <= UW3 ? 1 : (UW + UW2 - 1) / UW2;  // column sweeps
+    const int nround = (UH + per - 1) / per;
+    const bool tabled = none || (UW <= UMAX && UH <= UMAX && mf_sweeps_pay(g, mg, nsweep * nround, NT));
     if (tabled) {
-      // shift rows of a round, spread over the waves: up to two each, one
-      // each for unions that need the two-part lane layout and for images
-      // with a scale per pixel.  No barrier
-      // inside a round: a wave without shift rows goes on.
-      const bool one = kuni != 0.f && quni != 0.f;  // both images have one scale
-      const int per = NW * (one && UW <= UW3 ? NDW : 1);
-      for (int rr0 = 0; rr0 < (none ? 0 : UH); rr0 += per) {
+      // No barrier inside a round: a wave without shift rows goes on.
+      for (int it = 0; it < (none ? 0 : nsweep * nround); ++it) {
+        const int cc0 = it / nround * UW2, rr0 = (it - it / nround * nround) * per;
         const int nr = min(per, UH - rr0);
         const int nd = nr / NW + (wave < nr % NW ? 1 : 0);
         MfFrame f;
@@ -679,11 +694,12 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
         f.rec = rec;
         f.plane_bytes = (int)plane_bytes;
         f.dr0 = rr0 + wave * (nr / NW) + min(wave, nr % NW);
+        f.dc0 = cc0;
         f.row0 = Y0 + dmin_h + f.dr0;
         f.hr = hr;
         f.ngrp = mg.nc32 / CG;
         f.qpitch = mg.qpitch;
-        f.col0 = X0 + dmin_w;
+        f.col0 = X0 + dmin_w + cc0;
         f.s0 = s0;
         f.tqw = tqw;
         f.wp = wp;
@@ -745,9 +761,8 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
     const bool again = tabled;
     if (!again || __float_as_uint(kuni) == 0x80000000u || __float_as_uint(quni) == 0x80000000u) {
       if (again) __syncthreads();  // the frame's scores are written
-      // or a union too wide for the lanes or too tall for the queries' packed
-      // shifts: this frame's candidates one by one
-      // (inner products for both distances, as the top-k pass expects)
+      // or a union that costs more to sweep: this frame's candidates one by
+      // one (inner products for both distances, as the top-k pass expects)
       Geo gp = g;
       gp.dist = SNLS_DIST_PROD;
       for (int e = tid; e < qn * ws; e += NT) {

@@ -1,8 +1,8 @@
 """The matrix-core scores of the tiled search against the oracle where the
 kernel changes path: channel padding and chunk groups (8 to 130 channels per
 head), unions of shift columns at the edges of two and three key blocks and of
-the three lane layouts (17/18, 21/22, 32/33 columns), more shift rows than one
-round holds, strided queries, every patch size, and images whose pixels need
+the three lane layouts (17/18, 21/22, 32/33 columns) and of several sweeps, more
+shift rows than one round holds, strided queries, every patch size, and images whose pixels need
 scales of their own."""
 import numpy as np
 import pytest
@@ -55,6 +55,24 @@ def test_scores_at_path_edges(dev, ps, C, HD, ws, s0, s1, rows, cols):
     shp = (1, 2, C, 38, 43)
     q, k = (rng.standard_normal(shp, dtype=np.float32) for _ in range(2))
     fl = _flows(p, rows, cols, rng)
+    gd, gi = _search(q, k, fl, p, dev)
+    compare_topk(gd, gi, oracle.search(q, k, fl, p), p["k"])
+
+
+@pytest.mark.parametrize("ps,C,s0,s1,cols,dark", [(7, 64, 1, 1.0, 55, False), (7, 72, 2, 0.5, 56, False), (3, 33, 1, 1.0, 88, True),
+                                                  (5, 16, 3, 1.0, 60, False), (1, 32, 1, 1.0, 23, False), (1, 32, 1, 1.0, 70, False)])
+def test_unions_swept_by_columns(dev, ps, C, s0, s1, cols, dark):
+    """Unions of shift columns around one, two, three and four sweeps of 32
+    (windows of 9 add 9 columns, at half strides 5), also with scales per pixel."""
+    p = small_params(T=2, C=C, H=40, W=120, ws=9, wt=1, ps=ps, k=12, stride0=s0, stride1=s1)
+    rng = np.random.default_rng(ps + cols)
+    shp = (1, 2, C, 40, 120)
+    q, k = (rng.standard_normal(shp, dtype=np.float32) for _ in range(2))
+    if dark:
+        q[..., ::7, ::5] *= 1e-6
+    fl = rng.uniform(-2, 2, (1, 2, 2, 2, 40, 120)).astype(np.float32)
+    x = np.arange(120) % 20 >= 10
+    fl[:, :, :, 1] += np.where(x, cols - cols // 2, -(cols // 2)) - 0.5
     gd, gi = _search(q, k, fl, p, dev)
     compare_topk(gd, gi, oracle.search(q, k, fl, p), p["k"])
 

@@ -82,7 +82,7 @@ struct MfGeo {
   int tqh, tqw; // queries per tile
   int hr;       // halo rows
   int tiles_x, tiles_y;
-  int qpitch;   // bytes of a pixel record in LDS
+  int qpitch;   // bytes of a pixel's record (one or two chunks) in LDS
   int o_qs, o_d, o_tab, o_qi, o_ql, o_fl, o_dump, o_uni;  // LDS offsets (bytes)
   int wp, win;  // window table pitch and size of a query
 };
@@ -310,9 +310,10 @@ struct MfFrame {
   const float* kscale;
   int W, rec, plane_bytes;      // frame width; bytes of a pixel record and of a plane
   int row0;                     // frame row of (halo row 0, the wave's first shift row)
-  int H, hr, ngrp, qpitch;
+  int H, hr, qpitch;
   int dr0, dc0, col0;           // the wave's first shift row and column less the union's, frame column of product column 0
   int s0, tqw, wp;
+  int gi;                       // channel group (CG chunks) in the q halo
   float kuni, quni;             // scale of the key and query images (0: per pixel, in kscale and qsc)
 };
 
@@ -321,8 +322,10 @@ struct MfFrame {
 // reads key row s + row0 and pairs it with halo rows s, s - 1, ...; halo rows
 // outside [0, hr) (the first and last ND - 1 steps) are computed from a
 // clamped row: they enter only sums that are never written, and the loop has
-// no branches.
-template <int PS, int CG, bool S1, int ND, int NB, int NPART, bool ONE>
+// no branches.  ADD: the sums are added to those of the frame's earlier channel
+// groups (a read and a select per sum: 5 to 15% of a whole call where a run-time
+// flag made every call pay for them).
+template <int PS, int CG, bool S1, int ND, int NB, int NPART, bool ONE, bool ADD>
 SNLS_DEV void mf_stream(const MfFrame& f, const unsigned char* qlds, const float* qsc, float* dbuf, const int2* qi,
                         float* tab, float* dump0) {
   using namespace mf;
@@ -336,6 +339,7 @@ SNLS_DEV void mf_stream(const MfFrame& f, const unsigned char* qlds, const float
   const int part = min(lane / LW, NPART - 1);
   const int le = lane - part * LW;               // shift column (lane 63 of three parts: column 21, never read)
   const int xh = min(part * NXP, NX - NXP);      // first patch origin of this part
+  [[maybe_unused]] const int xdup = part * NXP - xh;  // its first ones that the part before has too
   const __amdgpu_buffer_rsrc_t k_rs =
       __builtin_amdgcn_make_buffer_rsrc((void*)f.kplane, (short)0, f.plane_bytes, 0x00020000);
   unsigned voff[NB];  // byte offsets of this lane's key columns (outside the frame: reads 0)
@@ -346,13 +350,13 @@ SNLS_DEV void mf_stream(const MfFrame& f, const unsigned char* qlds, const float
     voff[n] = in ? (unsigned)((lg * f.W + gx) * 16) : OOB;
   }
   half8 bh[NB][CG], bl[NB][CG];
-  // operand A of step s, channel group gi; rows outside the frame read 0
+  // operand A of step s; rows outside the frame read 0
   // (a scalar offset of the whole plane puts every lane past its end)
-  auto load_k = [&](int s, int gi) {
+  auto load_k = [&](int s) {
     const int gy = f.row0 + s;
     const bool in = gy >= 0 && gy < f.H;
     const int part4 = f.W * 64;  // bytes of the hi (or lo) pieces of a chunk
-    const int so = in ? gy * f.W * f.rec + gi * CG * 2 * part4 : f.plane_bytes;
+    const int so = in ? gy * f.W * f.rec + f.gi * CG * 2 * part4 : f.plane_bytes;
 #pragma unroll
     for (int c = 0; c < CG; ++c)
 #pragma unroll
@@ -401,7 +405,7 @@ SNLS_DEV void mf_stream(const MfFrame& f, const unsigned char* qlds, const float
   const unsigned char* const ap0 = qlds + lj * f.qpitch + lg * 16;
   const int qrow = HC * f.qpitch;
   const int nstep = f.hr + ND - 1;
-  load_k(0, 0);
+  load_k(0);
   auto step = [&](int s, auto phase) {
     constexpr int PH = decltype(phase)::value;
     f32x4 acc[ND][NB];
@@ -409,39 +413,32 @@ SNLS_DEV void mf_stream(const MfFrame& f, const unsigned char* qlds, const float
     for (int i = 0; i < ND; ++i)
 #pragma unroll
       for (int n = 0; n < NB; ++n) acc[i][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto products = [&](int gi) {
 #pragma unroll
-      for (int i = 0; i < ND; ++i) {
-        const unsigned char* ap = ap0 + min(max(s - i, 0), f.hr - 1) * qrow + gi * (CG * 128);
-        half8 ah[CG], al[CG];  // operand B
+    for (int i = 0; i < ND; ++i) {
+      const unsigned char* ap = ap0 + min(max(s - i, 0), f.hr - 1) * qrow;
+      half8 ah[CG], al[CG];  // operand B
 #pragma unroll
-        for (int c = 0; c < CG; ++c) {
-          ah[c] = *reinterpret_cast<const half8*>(ap + c * 128);
-          al[c] = *reinterpret_cast<const half8*>(ap + c * 128 + 64);
-        }
-        // the small products of all chunks first: their roundings are small too
-        auto mul = [&](const half8(&kk)[NB][CG], const half8(&qq)[CG], int c) {
-#pragma unroll
-          for (int n = 0; n < NB; ++n)
-            acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kk[n][c], qq[c], acc[i][n], 0, 0, 0);
-        };
-#pragma unroll
-        for (int c = 0; c < CG; ++c) mul(bl, al, c);
-#pragma unroll
-        for (int c = 0; c < CG; ++c) {
-          mul(bh, al, c);
-          mul(bl, ah, c);
-        }
-#pragma unroll
-        for (int c = 0; c < CG; ++c) mul(bh, ah, c);
+      for (int c = 0; c < CG; ++c) {
+        ah[c] = *reinterpret_cast<const half8*>(ap + c * 128);
+        al[c] = *reinterpret_cast<const half8*>(ap + c * 128 + 64);
       }
-    };
-    for (int gi = 0; gi + 1 < f.ngrp; ++gi) {
-      products(gi);
-      load_k(s, gi + 1);
+      // the small products of all chunks first: their roundings are small too
+      auto mul = [&](const half8(&kk)[NB][CG], const half8(&qq)[CG], int c) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+          acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kk[n][c], qq[c], acc[i][n], 0, 0, 0);
+      };
+#pragma unroll
+      for (int c = 0; c < CG; ++c) mul(bl, al, c);
+#pragma unroll
+      for (int c = 0; c < CG; ++c) {
+        mul(bh, al, c);
+        mul(bl, ah, c);
+      }
+#pragma unroll
+      for (int c = 0; c < CG; ++c) mul(bh, ah, c);
     }
-    products(f.ngrp - 1);
-    load_k(s + 1, 0);  // in flight during the sums below
+    load_k(s + 1);  // in flight during the sums below
     // The products of shift row i + 1 enter the wave's LDS block right behind
     // row i's reads (a wave's LDS accesses complete in order), so that they
     // are there when row i's sums are done.
@@ -481,8 +478,10 @@ SNLS_DEV void mf_stream(const MfFrame& f, const unsigned char* qlds, const float
           const unsigned u = (unsigned)(f.dr0 + i - (w[x].x >> 16)), c = (unsigned)(lc - (int)(short)w[x].x);
           bool ok = max(u, c) < (unsigned)f.wp;
           if (!S1) ok = ok && ((xok >> x) & 1);
+          if (ADD) ok = ok && x >= xdup;
           float* const at = ok ? tab + (w[x].y + cell) : dump;
-          *at = hb[x];
+          if constexpr (ADD) *at += hb[x];
+          else *at = hb[x];
         }
       }
     }
@@ -581,10 +580,12 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
     }
     fl[e] = F;
   }
-  {
-    const __amdgpu_buffer_rsrc_t q_rs = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(qs + slab(t) * g.HW * rec), (short)0, (int)plane_bytes, 0x00020000);
-    const int npix = hr * HC, n = npix * (rec / 16);
+  // the halo's records of channel group gi
+  const int npix = hr * HC, ngrp = CG > 1 ? mg.nc32 / CG : 1;
+  const __amdgpu_buffer_rsrc_t q_rs = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(qs + slab(t) * g.HW * rec), (short)0, (int)plane_bytes, 0x00020000);
+  auto load_halo = [&](int gi) {
+    const int n = npix * (CG * 8);
     for (int e0 = tid; e0 < n; e0 += 4 * NT) {  // four loads in flight
       u32x4 v[4];
       int at[4];
@@ -596,13 +597,15 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
         const bool in = e < n && gy >= 0 && gy < g.H && gx >= 0 && gx < g.W;
         at[i] = p * mg.qpitch + pc * 16;
         v[i] = __builtin_amdgcn_raw_buffer_load_b128(
-            q_rs, in ? (unsigned)(gy * g.W * rec + (pc * g.W + gx) * 16) : OOB, 0, 0);
+            q_rs, in ? (unsigned)(gy * g.W * rec + ((gi * CG * 8 + pc) * g.W + gx) * 16) : OOB, 0, 0);
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         if (e0 + i * NT < n) *reinterpret_cast<u32x4*>(qlds + at[i]) = v[i];
     }
-  }
+  };
+  int held = 0;  // the channel group in the halo
+  load_halo(0);
   __syncthreads();
   // a query's first integer shifts of a frame, and its last ones + 1.
   // Offsets that are not finite or absurdly large count as zero here; their
@@ -679,10 +682,19 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
     const int per = NW * (one && UW <= UW3 ? NDW : 1);
     const int nsweep = one && UW <= UW3 ? 1 : (UW + UW2 - 1) / UW2;  // column sweeps
     const int nround = (UH + per - 1) / per;
-    const bool tabled = none || (UW <= UMAX && UH <= UMAX && mf_sweeps_pay(g, mg, nsweep * nround, NT));
+    const bool tabled = none || (UW <= UMAX && UH <= UMAX && mf_sweeps_pay(g, mg, ngrp * nsweep * nround, NT));
     if (tabled) {
       // No barrier inside a round: a wave without shift rows goes on.
-      for (int it = 0; it < (none ? 0 : nsweep * nround); ++it) {
+      for (int go = 0; go < (none ? 0 : ngrp); ++go) {
+      // channel groups upwards and downwards in turn: a frame begins with the one that is there
+      const int gi = (fi & 1) ? ngrp - 1 - go : go;
+      if (gi != held) {
+        __syncthreads();  // the halo is no longer read
+        load_halo(gi);
+        held = gi;
+        __syncthreads();
+      }
+      for (int it = 0; it < nsweep * nround; ++it) {
         const int cc0 = it / nround * UW2, rr0 = (it - it / nround * nround) * per;
         const int nr = min(per, UH - rr0);
         const int nd = nr / NW + (wave < nr % NW ? 1 : 0);
@@ -697,7 +709,7 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
         f.dc0 = cc0;
         f.row0 = Y0 + dmin_h + f.dr0;
         f.hr = hr;
-        f.ngrp = mg.nc32 / CG;
+        f.gi = gi;
         f.qpitch = mg.qpitch;
         f.col0 = X0 + dmin_w + cc0;
         f.s0 = s0;
@@ -706,19 +718,30 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
         f.kuni = kuni;
         f.quni = quni;
         const int2* const qif = qi + (fi & 1) * qn;
+        auto stream = [&](auto nd_, auto nb_, auto npart_, auto one_) {
+          constexpr int ND = decltype(nd_)::value, NB = decltype(nb_)::value, NPART = decltype(npart_)::value;
+          constexpr bool ONE = decltype(one_)::value;
+          if (CG > 1 && go > 0) mf_stream<PS, CG, S1, ND, NB, NPART, ONE, (CG > 1)>(f, qlds, qsc, dbuf, qif, tab, dump);
+          else mf_stream<PS, CG, S1, ND, NB, NPART, ONE, false>(f, qlds, qsc, dbuf, qif, tab, dump);
+        };
+        constexpr std::integral_constant<int, 1> i1{};
+        constexpr std::integral_constant<int, 2> i2{};
+        constexpr std::integral_constant<int, 3> i3{};
+        constexpr std::integral_constant<int, NDW> iw{};
         if (!one) {
-          if (nd == 1) mf_stream<PS, CG, S1, 1, 3, 2, false>(f, qlds, qsc, dbuf, qif, tab, dump);
+          if (nd == 1) stream(i1, i3, i2, std::false_type{});
         } else if (UW <= 17) {  // 16 + UW - 1 key columns in two blocks
-          if (nd == 1) mf_stream<PS, CG, S1, 1, 2, 3, true>(f, qlds, qsc, dbuf, qif, tab, dump);
-          else if (nd == 2) mf_stream<PS, CG, S1, 2, 2, 3, true>(f, qlds, qsc, dbuf, qif, tab, dump);
-          else if (nd == 3 && NDW == 3) mf_stream<PS, CG, S1, NDW, 2, 3, true>(f, qlds, qsc, dbuf, qif, tab, dump);
+          if (nd == 1) stream(i1, i2, i3, std::true_type{});
+          else if (nd == 2) stream(i2, i2, i3, std::true_type{});
+          else if (nd == 3 && NDW == 3) stream(iw, i2, i3, std::true_type{});
         } else if (UW <= UW3) {
-          if (nd == 1) mf_stream<PS, CG, S1, 1, 3, 3, true>(f, qlds, qsc, dbuf, qif, tab, dump);
-          else if (nd == 2) mf_stream<PS, CG, S1, 2, 3, 3, true>(f, qlds, qsc, dbuf, qif, tab, dump);
-          else if (nd == 3 && NDW == 3) mf_stream<PS, CG, S1, NDW, 3, 3, true>(f, qlds, qsc, dbuf, qif, tab, dump);
+          if (nd == 1) stream(i1, i3, i3, std::true_type{});
+          else if (nd == 2) stream(i2, i3, i3, std::true_type{});
+          else if (nd == 3 && NDW == 3) stream(iw, i3, i3, std::true_type{});
         } else if (nd == 1) {
-          mf_stream<PS, CG, S1, 1, 3, 2, true>(f, qlds, qsc, dbuf, qif, tab, dump);
+          stream(i1, i3, i2, std::true_type{});
         }
+      }
       }
       __syncthreads();
       if (fi + 1 < nfr) set_queries(fi + 1);
@@ -796,7 +819,7 @@ static bool mf_geo(const Geo& g, int tqh, MfGeo* m) {
   m->hr = (tqh - 1) * g.s0 + g.ps;
   m->tiles_x = (g.nW + m->tqw - 1) / m->tqw;
   m->tiles_y = (g.nH + tqh - 1) / tqh;
-  m->qpitch = m->rec + 16;  // an odd number of 16-byte slots: consecutive pixels on different banks
+  m->qpitch = (m->nc32 > 1 ? 2 : 1) * 128 + 16;  // an odd number of 16-byte slots: consecutive pixels on different banks
   m->wp = g.ws + 2;
   m->win = m->wp * m->wp;
   const long long qn = (long long)m->tqh * m->tqw;

@@ -77,6 +77,21 @@ def test_unions_swept_by_columns(dev, ps, C, s0, s1, cols, dark):
     compare_topk(gd, gi, oracle.search(q, k, fl, p), p["k"])
 
 
+@pytest.mark.parametrize("ps,C,ws,s0,s1,cols,dist", [(7, 256, 9, 1, 1.0, 5, 0), (7, 193, 3, 1, 1.0, 14, 0), (5, 384, 9, 2, 0.5, 20, 0),
+                                                     (3, 512, 5, 1, 1.0, 31, 0), (6, 320, 7, 3, 1.0, 50, 0), (7, 200, 9, 1, 1.0, 8, 1),
+                                                     (1, 160, 9, 1, 1.0, 16, 0)])
+def test_heads_of_many_channels(dev, ps, C, ws, s0, s1, cols, dist):
+    """Three channel groups and more: the window tables collect the groups'
+    sums (lane layouts of two and three parts, one and several sweeps)."""
+    p = small_params(T=2, C=C, H=33, W=75, ws=ws, wt=1, ps=ps, k=12, stride0=s0, stride1=s1, dist_type=dist)
+    rng = np.random.default_rng(ps * C)
+    shp = (1, 2, C, 33, 75)
+    q, k = (rng.standard_normal(shp, dtype=np.float32) for _ in range(2))
+    fl = _flows(p, 5, cols, rng)
+    gd, gi = _search(q, k, fl, p, dev)
+    compare_topk(gd, gi, oracle.search(q, k, fl, p), p["k"])
+
+
 @pytest.mark.parametrize("H,s0", [(18100, 1), (18100, 8)])
 def test_tall_frames(dev, H, s0):
     """Valid offsets of one tile more than 16384 rows apart: a query's shift

@@ -7,46 +7,48 @@
 // shifts that the tile's windows read.  Here the contraction over the head's
 // channels runs on the matrix cores.
 //
-// Precision.  A fp32 value x, scaled by a power of two so that its image's
-// largest magnitude lies in [2^14, 2^15), is split into two fp16 numbers, hi
-// = fp16(x) and lo = fp16(x - hi): 22 to 24 significant
-// bits.  All four partial products are formed (v_mfma_f32_16x16x32_f16, fp32
-// accumulation), so the only error beyond the accumulation's is the rounding
-// of lo, unbiased; dropping lo * lo (three products) biases the scores of
-// near-copies and was measured worse (64x64 noise, 16 channels: relative
-// error 7.0e-8 against 4.9e-8).  With the 4-tap pass in 64 bits (one rounding)
-// the scores' error against 64-bit sums is below that of the fp32 vector-unit
-// kernel on every shape measured.
+// Precision.  A fp32 value is the sum of three bf16 numbers, each the nearest
+// to what the ones before leave (8 significant bits and a sign each, fp32's
+// exponents: no scale, whatever the range of an image or its channels).  Six of
+// the nine partial products are formed (v_mfma_f32_16x16x32_bf16, fp32
+// accumulation, the small ones first); the three left out are below 2^-25 of
+// the product and of either sign.  With the 4-tap pass in 64 bits (one
+// rounding) the scores' error against 64-bit sums is below that of the fp32
+// vector-unit kernel: 64x64 noise with 16 channels, P = 3: 4.4e-8 against
+// 4.7e-8; 96x96 with 32 channels, P = 3: 4.0e-8 against 4.7e-8, for channels of
+// one size as for channels 2^24 apart.  Two fp16 parts of values scaled by image
+// (four products) held 22 to 24 bits and lost channels below 2^-16 of the
+// image's largest value (9.7e-7 at 2^24); they took a third less matrix-core
+// time and key traffic (480x854, P = 7, 64 channels: 11.4 ms for the call, now
+// 15.1).
 //
-// Work split (one workgroup of 12 waves = one query tile of one (b, head, t),
-// looping over the frames of the window):
+// Work split (one workgroup = one query tile of one (b, head, t), looping over
+// the frames of the window; 12 waves for heads up to 32 channels, else 8):
 //  * the tile's halo of q -- hr rows of 16 pixels, tile rows (16 - P) / S_Q + 1
-//    queries wide -- sits in LDS in split form for all frames;
-//  * a wave owns one or two consecutive shift rows D_h.  It streams the key
-//    rows straight from memory into registers (matrix operand B: 16 key
-//    columns x the channels, 2 or 3 column blocks), one key row at a time;
-//    key row Y pairs with halo row y = Y - D_h for each of its shift rows,
-//    so one load serves them all, and the next row's load is in flight while
-//    the current one's sums are formed.  No workgroup barrier inside a frame;
+//    queries wide -- sits in LDS in split form, up to 64 channels of it; wider
+//    heads go through in groups of 64, each group's sums added to the tables;
+//  * a wave owns up to two (three: 8 waves and P < 5) consecutive shift rows
+//    D_h at a time.  It streams the key rows straight from memory into
+//    registers (matrix operand A: 16 key columns x the channels, 2 or 3 column
+//    blocks), one key row at a time; key row Y pairs with halo row y = Y - D_h
+//    for each of its shift rows, so one load serves them all, and the next
+//    row's load is in flight while the current one's sums are formed.  No
+//    workgroup barrier inside a round of shift rows;
 //  * the 16 x 48 products (x, X) of a (halo row, shift row) go through the
 //    wave's own LDS block, whose diagonals X - x = D_w the lanes read back:
 //    lane = (shift column, part of the tile's columns; 3 parts of 21 lanes
-//    for unions up to 21 shift columns, else 2 of 32).  The horizontal box
-//    sums are formed in registers, the vertical ones as a running tree over
-//    the halo rows (each row adds once: v, v + v', ... as in search_tile.hip),
-//    and every finished box sum goes to its query's window table in LDS;
+//    for unions up to 21 shift columns, else 2 of 32, swept 32 columns at a
+//    time).  The horizontal box sums are formed in registers, the vertical ones
+//    as a running tree over the halo rows (each row adds once: v, v + v', ... as
+//    in search_tile.hip), and every finished box sum goes to its query's window
+//    table in LDS;
 //  * the 4-tap pass writes the scores of the frame to the workspace rows.
 //
-// Measured (480x854, T = 5, 64 channels, P = 7, Ws = 9): 11.8 ms with the
-// split copies (0.4 ms) against 20.3 ms on the vector units, whose products
-// alone are 60% of its instructions.  A tile-frame takes about 80,000 cycles:
-// 53,000 streaming (per step and wave of two shift rows: 1,060 for the
-// products -- 614 of them matrix-core time --, 1,380 for the sums, 450 loop
-// and operand issue), 12,000 waiting for the wave with one row more, 9,400 in
-// the 4-tap pass, the rest set-up.  The matrix cores are busy a fifth of the
-// time: the chain product -> LDS -> sums bounds it, at 2 or 3 waves per SIMD.
-// The operand's layout matters: with a pixel's pieces contiguous (16 lanes of
-// a load on 16 cache lines) the same kernel took 20.9 ms.
+// Measured (480x854, T = 5, 64 channels, P = 7, Ws = 9, the whole search): 15.1 ms
+// against 25 ms with the scores on the vector units.  A step of a wave of two
+// shift rows takes about 4,300 cycles: 820 to issue the vector instructions, 790
+// of matrix cores, the rest waits, at 2 waves per SIMD -- without the key loads
+// (stale operands) the call takes 3.2 ms less, without the third parts 3.9.
 #include <math.h>
 #include <type_traits>
 
@@ -57,33 +59,36 @@ namespace snls {
 namespace mf {
 // Waves per workgroup and shift rows per wave: 12 waves (3 per SIMD, 168
 // VGPRs each) of up to 2 rows for records of one chunk; 8 (2 per SIMD, 256
-// VGPRs) of up to 3 rows where two chunks' operands are held (480x854, 64
-// channels, P = 7: 12.4 ms, with 12 waves 13.0 and more; 128x128, 32
-// channels: 12 waves 1.29 ms a step, 8 waves 1.37).
+// VGPRs) where two chunks' operands are held (480x854, 64 channels, P = 7: 15.1
+// ms for the call, with 12 waves 22.3), of up to 3 rows for P < 5 (256x256, P =
+// 3: 0.62 and 0.64 ms) and 2 above, whose vertical sums take more registers
+// (480x854, P = 7: 3 rows 15.7 ms; P = 5 at S_Q = 2: 2.5 and 2.2 ms).
 constexpr int waves(int CG) { return CG == 1 ? 12 : 8; }
-constexpr int rows_per_wave(int CG) { return CG == 1 ? 2 : 3; }
-constexpr int HC = 16;           // halo columns = rows of operand A
+constexpr int rows_per_wave(int PS, int CG) { return CG > 1 && PS < 5 ? 3 : 2; }
+constexpr int HC = 16;           // halo columns = columns of operand B
 constexpr int UW3 = 21;          // shift columns with three column parts (one per lane of a part)
 constexpr int UW2 = 32;          // ... with two (16 + 32 - 1 <= 48 key columns): wider unions are swept 32 at a time
 constexpr int UMAX = 16383;      // shift rows or columns of a union: a query's first one, relative to the union's, has 16 bits
 constexpr int DP = 52;           // pitch of a product row in LDS (4 DP = 16 mod 64: the writes' banks)
 constexpr int DBUF = HC * DP;    // floats per wave
 constexpr int LDS_BYTES = 160 * 1024;
+constexpr int PARTS = 3;         // bf16 parts of a value
+constexpr int CHUNK = PARTS * 64;  // bytes of a pixel's 32 channels
 
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 }  // namespace mf
 
 // Geometry of the split copies and of the tiles.
 struct MfGeo {
-  int nc32;     // 32-channel chunks of a pixel record (hi 64 bytes, lo 64 bytes each)
+  int nc32;     // 32-channel chunks of a pixel record (three parts of 64 bytes each)
   int rec;      // bytes of a pixel record
   int tqh, tqw; // queries per tile
   int hr;       // halo rows
   int tiles_x, tiles_y;
   int qpitch;   // bytes of a pixel's record (one or two chunks) in LDS
-  int o_qs, o_d, o_tab, o_qi, o_ql, o_fl, o_dump, o_uni;  // LDS offsets (bytes)
+  int o_d, o_tab, o_qi, o_ql, o_fl, o_dump, o_uni;  // LDS offsets (bytes)
   int wp, win;  // window table pitch and size of a query
 };
 
@@ -91,78 +96,25 @@ struct MfGeo {
 static int mf_chunks(const Geo& g) { return g.Ch <= 32 ? 1 : 2 * ((g.Ch + 63) / 64); }
 
 // ---- split copies ----
-//
-// Scales.  One power of two for a whole image (b, t, head) brings its largest
-// magnitude into [2^14, 2^15), provided that no pixel's largest channel lies
-// below 2^-12 of that (pixels of zeros aside): fp16 subnormals then still hold
-// every pixel to 2^-27 of its largest channel.  An image with a wider range
-// gets a scale per pixel, and its products are scaled pixel by pixel.
-//
-// The statistics of an image come from up to kStatBlocks workgroups, each
-// writing the largest and the smallest non-zero of its pixels' largest
-// magnitudes; every later workgroup reduces them for itself.
-constexpr int kStatBlocks = 256;
 
-// One thread per pixel, its channels' loads in flight together (480x854, 64
-// channels: 0.69 ms with 64 workgroups an image and 4 threads a pixel).
-SNLS_DEV float mf_pixel_max(const float* __restrict__ src, const Geo& g, long long p) {
-  float m = 0.f;
-  int c = 0;
-  for (; c + 8 <= g.Ch; c += 8) {
-    float v[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = src[(long long)(c + i) * g.HW + p];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(v[i]));
-  }
-  for (; c < g.Ch; ++c) m = fmaxf(m, fabsf(src[(long long)c * g.HW + p]));
-  return m;
-}
-
-__global__ void __launch_bounds__(256) mf_stats_kernel(const float* __restrict__ x, Geo g, float2* __restrict__ stats) {
-  __shared__ float2 part[4];
-  const long long slab = blockIdx.y;  // (b*T + t)*HD + hd
-  const int hd = (int)(slab % g.HD);
-  const float* src = x + ((slab / g.HD) * g.C + (long long)hd * g.Ch) * g.HW;
-  float hi = 0.f, lo = INFINITY;
-  for (long long p = (long long)blockIdx.x * 256 + threadIdx.x; p < g.HW; p += (long long)gridDim.x * 256) {
-    const float m = mf_pixel_max(src, g, p);
-    hi = fmaxf(hi, m);
-    if (m > 0.f) lo = fminf(lo, m);
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    hi = fmaxf(hi, __shfl_xor(hi, off));
-    lo = fminf(lo, __shfl_xor(lo, off));
-  }
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = make_float2(hi, lo);
-  __syncthreads();
-  if (threadIdx.x == 0)
-    stats[slab * kStatBlocks + blockIdx.x] =
-        make_float2(fmaxf(fmaxf(part[0].x, part[1].x), fmaxf(part[2].x, part[3].x)),
-                    fminf(fminf(part[0].y, part[1].y), fminf(part[2].y, part[3].y)));
-}
-
-// Power-of-two factors for a largest magnitude m: up brings it into [2^14,
-// 2^15) (for 2^-112 and above), down takes it back.
-SNLS_DEV void mf_factors(float m, float* up, float* down) {
-  int e = (int)((__float_as_uint(m) >> 23) & 255u) - 127;
-  e = min(max(e, -112), 127);
-  if (m == 0.f) e = 14;
-  *up = __uint_as_float((unsigned)(127 + 14 - e) << 23);
-  // 2^(e - 14) by two factors, neither of them denormal
-  const int e1 = max(e, -100);
-  *down = __uint_as_float((unsigned)(127 + e1) << 23) * __uint_as_float((unsigned)(127 + (e - e1) - 14) << 23);
+// The three bf16 parts of a value, which sum to it: each the nearest bf16 to
+// what the parts before leave (8 + 8 + 8 significant bits; values below 2^-110
+// lose their last bits to the denormal range).  A value that bf16 would round
+// to infinity starts from the largest finite one; the parts of an infinity or
+// a NaN after the first are 0.
+SNLS_DEV void mf_parts(float v, __bf16 (&p)[mf::PARTS]) {
+  const bool fin = fabsf(v) < INFINITY;
+  p[0] = (__bf16)(fin ? fminf(fmaxf(v, -0x1.fep127f), 0x1.fep127f) : v);
+  const float r = fin ? v - (float)p[0] : 0.f;
+  p[1] = (__bf16)r;
+  p[2] = (__bf16)(r - (float)p[1]);
 }
 
 // One workgroup = 64 pixels of one (b, t, head): channels x pixels through
-// LDS, 64 channels at a time, then 8 channels per thread are scaled, split
-// and written as two 16-byte pieces.  info: the image's scale, or 0 when
-// its pixels have their own (in scale); -0 where some of them are infinite.
+// LDS, 64 channels at a time, then 8 channels per thread are split and written
+// as three 16-byte pieces.
 __global__ void __launch_bounds__(256) mf_split_kernel(const float* __restrict__ x, Geo g, int nc32,
-                                                       const float2* __restrict__ stats, int nstat,
-                                                       unsigned char* __restrict__ xs, float* __restrict__ scale,
-                                                       float* __restrict__ info) {
+                                                       unsigned char* __restrict__ xs) {
   using namespace mf;
   __shared__ float tile[64][65];
   const long long slab = blockIdx.y;  // (b*T + t)*HD + hd
@@ -171,34 +123,14 @@ __global__ void __launch_bounds__(256) mf_split_kernel(const float* __restrict__
   const float* src = x + ((slab / g.HD) * g.C + (long long)hd * g.Ch) * g.HW;
   const int px = threadIdx.x & 63, qt = threadIdx.x >> 6;
   const bool pin = p0 + px < g.HW;
-  const int rec = nc32 * 128;
-  // row y of the plane: 16-byte pieces (8 channels, hi or lo) of its pixels,
-  // piece after piece: [32-channel chunk][hi, lo][4 pieces][W]
+  const int rec = nc32 * CHUNK;
+  // row y of the plane: 16-byte pieces (8 channels of one part) of its pixels,
+  // piece after piece: [32-channel chunk][part][4 pieces][W]
   const int p = (int)p0 + px;
   const int y = p / g.W;
   unsigned char* dst = xs + slab * g.HW * rec + ((long long)y * g.W * rec + (long long)(p - y * g.W) * 16);
   const long long pst = (long long)g.W * 16;  // bytes from piece to piece
   const int nch = nc32 * 32;                  // channels with padding
-  float hi = 0.f, lo = INFINITY;
-  for (int i = px; i < nstat; i += 64) {
-    const float2 st = stats[slab * kStatBlocks + i];
-    hi = fmaxf(hi, st.x);
-    lo = fminf(lo, st.y);
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    hi = fmaxf(hi, __shfl_xor(hi, off));
-    lo = fminf(lo, __shfl_xor(lo, off));
-  }
-  const bool one = !(lo < hi * 0x1p-12f) && hi < INFINITY;  // the same for every workgroup of the image
-  float up, down;
-  if (one) {
-    mf_factors(hi, &up, &down);
-  } else {
-    mf_factors(pin ? mf_pixel_max(src, g, p0 + px) : 0.f, &up, &down);  // (the same for the four threads of a pixel)
-    if (qt == 0 && pin) scale[slab * g.HW + p0 + px] = down;
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) info[slab] = one ? down : (hi < INFINITY ? 0.f : -0.f);
   for (int c0 = 0; c0 < nch; c0 += 64) {
     if (c0) __syncthreads();
     for (int i = qt; i < 64; i += 4) {
@@ -210,18 +142,17 @@ __global__ void __launch_bounds__(256) mf_split_kernel(const float* __restrict__
     // consecutive 16 bytes
     for (int pc = qt; pc < min(nch - c0, 64) / 8; pc += 4) {
       if (!pin) continue;
-      half8 h8, l8;
+      bf8 part[PARTS];
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const float v = tile[8 * pc + i][px] * up;
-        const _Float16 h = (_Float16)v;
-        const float r = v - (float)h;
-        h8[i] = h;
-        l8[i] = (_Float16)(r == r ? r : 0.f);  // (infinities: their scores are formed again from q and k)
+        __bf16 e[PARTS];
+        mf_parts(tile[8 * pc + i][px], e);
+#pragma unroll
+        for (int n = 0; n < PARTS; ++n) part[n][i] = e[n];
       }
-      unsigned char* o = dst + ((c0 / 32 + pc / 4) * 8 + (pc & 3)) * pst;
-      *reinterpret_cast<half8*>(o) = h8;
-      *reinterpret_cast<half8*>(o + 4 * pst) = l8;
+      unsigned char* o = dst + ((c0 / 32 + pc / 4) * (4 * PARTS) + (pc & 3)) * pst;
+#pragma unroll
+      for (int n = 0; n < PARTS; ++n) *reinterpret_cast<bf8*>(o + 4 * n * pst) = part[n];
     }
   }
 }
@@ -306,15 +237,14 @@ struct RunBox {
 
 // What the waves of a workgroup need of one frame step (uniform values).
 struct MfFrame {
-  const unsigned char* kplane;  // split key plane of the frame, its scales
-  const float* kscale;
+  const unsigned char* kplane;  // split key plane of the frame
   int W, rec, plane_bytes;      // frame width; bytes of a pixel record and of a plane
   int row0;                     // frame row of (halo row 0, the wave's first shift row)
   int H, hr, qpitch;
-  int dr0, dc0, col0;           // the wave's first shift row and column less the union's, frame column of product column 0
+  int dr0, dc0;                 // the wave's first shift row and column less the union's
+  int col0, ncol;               // frame column of product column 0; product columns that the union needs
   int s0, tqw, wp;
   int gi;                       // channel group (CG chunks) in the q halo
-  float kuni, quni;             // scale of the key and query images (0: per pixel, in kscale and qsc)
 };
 
 // The box sums of ND consecutive shift rows for the whole tile, NB blocks of
@@ -325,14 +255,16 @@ struct MfFrame {
 // no branches.  ADD: the sums are added to those of the frame's earlier channel
 // groups (a read and a select per sum: 5 to 15% of a whole call where a run-time
 // flag made every call pay for them).
-template <int PS, int CG, bool S1, int ND, int NB, int NPART, bool ONE, bool ADD>
-SNLS_DEV void mf_stream(const MfFrame& f, const unsigned char* qlds, const float* qsc, float* dbuf, const int2* qi,
-                        float* tab, float* dump0) {
+template <int PS, int CG, bool S1, int ND, int NB, int NPART, bool ADD>
+SNLS_DEV void mf_stream(const MfFrame& f, const unsigned char* qlds, float* dbuf, const int2* qi, float* tab,
+                        float* dump0) {
   using namespace mf;
   constexpr int NX = HC - PS + 1;                // patch origins per halo row
   constexpr int NXP = (NX + NPART - 1) / NPART;  // ... of a part (neighbouring parts may share some)
   constexpr int NV = NXP + PS - 1;               // products a lane reads per row
   constexpr int LW = NPART == 3 ? UW3 : UW2;     // lanes of a part
+  constexpr bool LATE = PS == 7 && CG == 1;  // the keys' third parts are not in flight during the sums
+  constexpr bool INTER = CG > 1;             // the products of all rows side by side
   constexpr unsigned OOB = 0x80000000u;
   const int lane = threadIdx.x & 63;
   const int lj = lane & 15, lg = lane >> 4;
@@ -342,29 +274,29 @@ SNLS_DEV void mf_stream(const MfFrame& f, const unsigned char* qlds, const float
   [[maybe_unused]] const int xdup = part * NXP - xh;  // its first ones that the part before has too
   const __amdgpu_buffer_rsrc_t k_rs =
       __builtin_amdgcn_make_buffer_rsrc((void*)f.kplane, (short)0, f.plane_bytes, 0x00020000);
-  unsigned voff[NB];  // byte offsets of this lane's key columns (outside the frame: reads 0)
+  unsigned voff[NB];  // byte offsets of this lane's key columns (outside the frame or the union: reads 0)
 #pragma unroll
   for (int n = 0; n < NB; ++n) {
     const int gx = f.col0 + 16 * n + lj;
-    const bool in = gx >= 0 && gx < f.W;
+    const bool in = gx >= 0 && gx < f.W && 16 * n + lj < f.ncol;
     voff[n] = in ? (unsigned)((lg * f.W + gx) * 16) : OOB;
   }
-  half8 bh[NB][CG], bl[NB][CG];
-  // operand A of step s; rows outside the frame read 0
+  bf8 kk[PARTS][NB][CG];
+  // parts e0 .. e1 - 1 of operand A of step s; rows outside the frame read 0
   // (a scalar offset of the whole plane puts every lane past its end)
-  auto load_k = [&](int s) {
+  auto load_k = [&](int s, int e0, int e1) {
     const int gy = f.row0 + s;
     const bool in = gy >= 0 && gy < f.H;
-    const int part4 = f.W * 64;  // bytes of the hi (or lo) pieces of a chunk
-    const int so = in ? gy * f.W * f.rec + f.gi * CG * 2 * part4 : f.plane_bytes;
+    const int part4 = f.W * 64;  // bytes of one part's pieces of a chunk
+    const int so = in ? gy * f.W * f.rec + f.gi * CG * PARTS * part4 : f.plane_bytes;
 #pragma unroll
-    for (int c = 0; c < CG; ++c)
+    for (int e = e0; e < e1; ++e)
 #pragma unroll
-      for (int n = 0; n < NB; ++n) {
-        const int sc = in ? so + c * 2 * part4 : so;
-        bh[n][c] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(k_rs, voff[n], sc, 0));
-        bl[n][c] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(k_rs, voff[n], in ? sc + part4 : so, 0));
-      }
+      for (int c = 0; c < CG; ++c)
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+          kk[e][n][c] = __builtin_bit_cast(
+              bf8, __builtin_amdgcn_raw_buffer_load_b128(k_rs, voff[n], in ? so + (c * PARTS + e) * part4 : so, 0));
   };
   RunBox<PS> st[ND][NXP];
 #pragma unroll
@@ -384,28 +316,10 @@ SNLS_DEV void mf_stream(const MfFrame& f, const unsigned char* qlds, const float
     jx[x] = ok ? j : 0;
     xok |= (ok ? 1u : 0u) << x;
   }
-  // images with a scale per pixel: the products of key row s and halo row y scaled back
-  auto scale_products = [&](f32x4(&a)[NB], int s, int y) {
-    const __amdgpu_buffer_rsrc_t s_rs =
-        __builtin_amdgcn_make_buffer_rsrc((void*)f.kscale, (short)0, f.plane_bytes / f.rec * 4, 0x00020000);
-    const float eq = f.quni != 0.f ? f.quni : qsc[min(max(y, 0), f.hr - 1) * HC + lj];
-    const int gy = f.row0 + s;
-#pragma unroll
-    for (int n = 0; n < NB; ++n)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int gx = f.col0 + 16 * n + 4 * lg + u;
-        const bool in = gy >= 0 && gy < f.H && gx >= 0 && gx < f.W;
-        const unsigned off = in && f.kuni == 0.f ? (unsigned)((gy * f.W + gx) * 4) : OOB;
-        const float ek = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(s_rs, off, 0, 0));
-        // in 64 bits: two scales may leave fp32's range where the product does not
-        a[n][u] = (float)((double)a[n][u] * ((double)(f.kuni != 0.f ? f.kuni : ek) * (double)eq));
-      }
-  };
   const unsigned char* const ap0 = qlds + lj * f.qpitch + lg * 16;
   const int qrow = HC * f.qpitch;
   const int nstep = f.hr + ND - 1;
-  load_k(0);
+  load_k(0, 0, LATE ? 2 : PARTS);
   auto step = [&](int s, auto phase) {
     constexpr int PH = decltype(phase)::value;
     f32x4 acc[ND][NB];
@@ -413,38 +327,76 @@ SNLS_DEV void mf_stream(const MfFrame& f, const unsigned char* qlds, const float
     for (int i = 0; i < ND; ++i)
 #pragma unroll
       for (int n = 0; n < NB; ++n) acc[i][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // The large products last: the others' roundings are small.  The next
+    // step's keys are in flight during this step's sums; where 168 registers
+    // cannot hold them (P = 7 with 12 waves) their third parts are loaded behind
+    // the first products (128x128, 32 channels: 0.54 -> 0.50 ms).  With 8 waves
+    // the products of all rows go side by side (480x854, P = 7: 16.0 -> 15.1 ms),
+    // their operand B held one part at a time.
+    auto mul = [&](int i, int ek, const bf8(&qq)[CG]) {
 #pragma unroll
-    for (int i = 0; i < ND; ++i) {
-      const unsigned char* ap = ap0 + min(max(s - i, 0), f.hr - 1) * qrow;
-      half8 ah[CG], al[CG];  // operand B
-#pragma unroll
-      for (int c = 0; c < CG; ++c) {
-        ah[c] = *reinterpret_cast<const half8*>(ap + c * 128);
-        al[c] = *reinterpret_cast<const half8*>(ap + c * 128 + 64);
-      }
-      // the small products of all chunks first: their roundings are small too
-      auto mul = [&](const half8(&kk)[NB][CG], const half8(&qq)[CG], int c) {
+      for (int c = 0; c < CG; ++c)
 #pragma unroll
         for (int n = 0; n < NB; ++n)
-          acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kk[n][c], qq[c], acc[i][n], 0, 0, 0);
+          acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk[ek][n][c], qq[c], acc[i][n], 0, 0, 0);
+    };
+    auto load_q = [&](int i, int e, bf8(&qq)[CG]) {  // operand B: part e of row i
+      const unsigned char* ap = ap0 + min(max(s - i, 0), f.hr - 1) * qrow + e * 64;
+#pragma unroll
+      for (int c = 0; c < CG; ++c) qq[c] = *reinterpret_cast<const bf8*>(ap + c * CHUNK);
+    };
+    if constexpr (LATE) load_k(s, 2, 3);
+    if constexpr (INTER) {
+      bf8 qq[ND][CG];
+      auto take = [&](int e) {
+#pragma unroll
+        for (int i = 0; i < ND; ++i) load_q(i, e, qq[i]);
       };
+      auto mul_all = [&](int ek) {
 #pragma unroll
-      for (int c = 0; c < CG; ++c) mul(bl, al, c);
+        for (int i = 0; i < ND; ++i) mul(i, ek, qq[i]);
+      };
+      take(2);
+      mul_all(0);
+      take(1);
+      mul_all(1);
+      mul_all(0);
+      take(0);
+      mul_all(1);
+      mul_all(2);
+      mul_all(0);
+    } else {
 #pragma unroll
-      for (int c = 0; c < CG; ++c) {
-        mul(bh, al, c);
-        mul(bl, ah, c);
+      for (int i = 0; i < ND; ++i) {
+        bf8 q0[CG], q1[CG], q2[CG];
+        load_q(i, 2, q2);
+        load_q(i, 1, q1);
+        load_q(i, 0, q0);
+        mul(i, 0, q2);
+        mul(i, 1, q1);
+        mul(i, 1, q0);
+        mul(i, 0, q1);
+        if constexpr (!LATE) {
+          mul(i, 2, q0);
+          mul(i, 0, q0);
+        }
       }
+      if constexpr (LATE) {
 #pragma unroll
-      for (int c = 0; c < CG; ++c) mul(bh, ah, c);
+        for (int i = 0; i < ND; ++i) {
+          bf8 q0[CG];
+          load_q(i, 0, q0);
+          mul(i, 2, q0);
+          mul(i, 0, q0);
+        }
+      }
     }
-    load_k(s + 1);  // in flight during the sums below
+    load_k(s + 1, 0, LATE ? 2 : PARTS);  // in flight during the sums below
     // The products of shift row i + 1 enter the wave's LDS block right behind
     // row i's reads (a wave's LDS accesses complete in order), so that they
     // are there when row i's sums are done.
     auto put_products = [&](int i) {
       // row x = lj, columns X = 16 n + 4 lg ..
-      if constexpr (!ONE) scale_products(acc[i], s, s - i);
 #pragma unroll
       for (int n = 0; n < NB; ++n) *reinterpret_cast<f32x4*>(dw + 16 * n) = acc[i][n];
       wave_lds_sync();
@@ -515,14 +467,13 @@ SNLS_DEV bool mf_sweeps_pay(const Geo& g, const MfGeo& mg, int rounds, int nt) {
 template <int PS, int CG, bool S1>
 __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_mfma_scores_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const unsigned char* __restrict__ qs,
-    const float* __restrict__ qscale, const float* __restrict__ qinfo, const unsigned char* __restrict__ ks,
-    const float* __restrict__ kscale, const float* __restrict__ kinfo, const float* __restrict__ flows, Geo g, MfGeo mg, float* __restrict__ scores, int pitch) {
+    const unsigned char* __restrict__ ks, const float* __restrict__ flows, Geo g, MfGeo mg, float* __restrict__ scores,
+    int pitch) {
   using namespace mf;
   constexpr int LO = -(PS / 2);
-  constexpr int NW = waves(CG), NT = NW * 64, NDW = rows_per_wave(CG);
+  constexpr int NW = waves(CG), NT = NW * 64, NDW = rows_per_wave(PS, CG);
   __shared__ __attribute__((aligned(16))) unsigned char smem[LDS_BYTES];
   unsigned char* const qlds = smem;
-  float* const qsc = reinterpret_cast<float*>(smem + mg.o_qs);
   float* const tab = reinterpret_cast<float*>(smem + mg.o_tab);
   float2* const fl = reinterpret_cast<float2*>(smem + mg.o_fl);  // offsets: [frame of the window][query]
   // two buffers (this frame's and the next one's):
@@ -530,7 +481,9 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
   int2* const qi = reinterpret_cast<int2*>(smem + mg.o_qi);
   int2* const ql = reinterpret_cast<int2*>(smem + mg.o_ql);  // a query's first shift row and column
   float* const dump = reinterpret_cast<float*>(smem + mg.o_dump);
-  int* const uni = reinterpret_cast<int*>(smem + mg.o_uni);  // min N_h, max N_h, min N_w, max N_w of each frame
+  // min N_h, max N_h, min N_w, max N_w of each frame; the last frame step (from 1) with a score that is not finite
+  int* const uni = reinterpret_cast<int*>(smem + mg.o_uni);
+  int* const nonfin = uni + 4 * (2 * g.wt + 1);
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -561,14 +514,8 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
 
   auto slab = [&](int tt) { return ((long long)b * g.T + tt) * g.HD + hd; };
 
-  // ---- the halo of q (split records and scales), the tile's offsets ----
-  const float quni = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(qinfo[slab(t)])));
-  if (quni == 0.f)
-    for (int p = tid; p < hr * HC; p += NT) {
-      const int gy = Y0 + p / HC, gx = X0 + p % HC;
-      const bool in = gy >= 0 && gy < g.H && gx >= 0 && gx < g.W;
-      qsc[p] = in ? qscale[slab(t) * g.HW + (long long)gy * g.W + gx] : 0.f;
-    }
+  // ---- the halo of q (split records), the tile's offsets ----
+  if (tid == 0) *nonfin = 0;
   for (int e = tid; e < nfr * qn; e += NT) {
     const int fi = e / qn, j = e - fi * qn, dt = dt0 + fi;
     const int h = y0 + s0 * (j / tqw), w = x0 + s0 * (j % tqw);
@@ -585,7 +532,7 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
   const __amdgpu_buffer_rsrc_t q_rs = __builtin_amdgcn_make_buffer_rsrc(
       (void*)(qs + slab(t) * g.HW * rec), (short)0, (int)plane_bytes, 0x00020000);
   auto load_halo = [&](int gi) {
-    const int n = npix * (CG * 8);
+    const int n = npix * (CG * 4 * PARTS);
     for (int e0 = tid; e0 < n; e0 += 4 * NT) {  // four loads in flight
       u32x4 v[4];
       int at[4];
@@ -597,7 +544,7 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
         const bool in = e < n && gy >= 0 && gy < g.H && gx >= 0 && gx < g.W;
         at[i] = p * mg.qpitch + pc * 16;
         v[i] = __builtin_amdgcn_raw_buffer_load_b128(
-            q_rs, in ? (unsigned)(gy * g.W * rec + ((gi * CG * 8 + pc) * g.W + gx) * 16) : OOB, 0, 0);
+            q_rs, in ? (unsigned)(gy * g.W * rec + ((gi * CG * 4 * PARTS + pc) * g.W + gx) * 16) : OOB, 0, 0);
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i)
@@ -674,13 +621,10 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
     const int UH = dmax_h - dmin_h + 1, UW = dmax_w - dmin_w + 1;
     const bool none = UH <= 0 || UW <= 0;  // every cell of the frame is invalid
     const float2* const ff = fl + fi * qn;
-    const float kuni = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(kinfo[slab(t2)])));
-    const bool one = kuni != 0.f && quni != 0.f;  // both images have one scale
-    // shift rows of a round, spread over the waves: up to two each, one
-    // each for unions that need the two-part lane layout and for images
-    // with a scale per pixel.
-    const int per = NW * (one && UW <= UW3 ? NDW : 1);
-    const int nsweep = one && UW <= UW3 ? 1 : (UW + UW2 - 1) / UW2;  // column sweeps
+    // shift rows of a round, spread over the waves: up to NDW each, one each
+    // for unions that need the two-part lane layout
+    const int per = NW * (UW <= UW3 ? NDW : 1);
+    const int nsweep = UW <= UW3 ? 1 : (UW + UW2 - 1) / UW2;  // column sweeps
     const int nround = (UH + per - 1) / per;
     const bool tabled = none || (UW <= UMAX && UH <= UMAX && mf_sweeps_pay(g, mg, ngrp * nsweep * nround, NT));
     if (tabled) {
@@ -700,7 +644,6 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
         const int nd = nr / NW + (wave < nr % NW ? 1 : 0);
         MfFrame f;
         f.kplane = ks + slab(t2) * g.HW * rec;
-        f.kscale = kscale + slab(t2) * g.HW;
         f.W = g.W;
         f.H = g.H;
         f.rec = rec;
@@ -712,43 +655,38 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
         f.gi = gi;
         f.qpitch = mg.qpitch;
         f.col0 = X0 + dmin_w + cc0;
+        f.ncol = HC - 1 + UW - cc0;
         f.s0 = s0;
         f.tqw = tqw;
         f.wp = wp;
-        f.kuni = kuni;
-        f.quni = quni;
         const int2* const qif = qi + (fi & 1) * qn;
-        auto stream = [&](auto nd_, auto nb_, auto npart_, auto one_) {
+        auto stream = [&](auto nd_, auto nb_, auto npart_) {
           constexpr int ND = decltype(nd_)::value, NB = decltype(nb_)::value, NPART = decltype(npart_)::value;
-          constexpr bool ONE = decltype(one_)::value;
-          if (CG > 1 && go > 0) mf_stream<PS, CG, S1, ND, NB, NPART, ONE, (CG > 1)>(f, qlds, qsc, dbuf, qif, tab, dump);
-          else mf_stream<PS, CG, S1, ND, NB, NPART, ONE, false>(f, qlds, qsc, dbuf, qif, tab, dump);
+          if (CG > 1 && go > 0) mf_stream<PS, CG, S1, ND, NB, NPART, (CG > 1)>(f, qlds, dbuf, qif, tab, dump);
+          else mf_stream<PS, CG, S1, ND, NB, NPART, false>(f, qlds, dbuf, qif, tab, dump);
         };
         constexpr std::integral_constant<int, 1> i1{};
         constexpr std::integral_constant<int, 2> i2{};
         constexpr std::integral_constant<int, 3> i3{};
         constexpr std::integral_constant<int, NDW> iw{};
-        if (!one) {
-          if (nd == 1) stream(i1, i3, i2, std::false_type{});
-        } else if (UW <= 17) {  // 16 + UW - 1 key columns in two blocks
-          if (nd == 1) stream(i1, i2, i3, std::true_type{});
-          else if (nd == 2) stream(i2, i2, i3, std::true_type{});
-          else if (nd == 3 && NDW == 3) stream(iw, i2, i3, std::true_type{});
+        if (UW <= 17) {  // 16 + UW - 1 key columns in two blocks
+          if (nd == 1) stream(i1, i2, i3);
+          else if (nd == 2) stream(i2, i2, i3);
+          else if (nd == 3 && NDW == 3) stream(iw, i2, i3);
         } else if (UW <= UW3) {
-          if (nd == 1) stream(i1, i3, i3, std::true_type{});
-          else if (nd == 2) stream(i2, i3, i3, std::true_type{});
-          else if (nd == 3 && NDW == 3) stream(iw, i3, i3, std::true_type{});
+          if (nd == 1) stream(i1, i3, i3);
+          else if (nd == 2) stream(i2, i3, i3);
+          else if (nd == 3 && NDW == 3) stream(iw, i3, i3);
         } else if (nd == 1) {
-          stream(i1, i3, i2, std::true_type{});
+          stream(i1, i3, i2);
         }
       }
       }
       __syncthreads();
       if (fi + 1 < nfr) set_queries(fi + 1);
-      // the images' scales, where the sums have not been scaled back yet
-      const double back = kuni != 0.f && quni != 0.f ? (double)kuni * (double)quni : 1.0;
       // ---- 4-tap combination and exact validity: one thread per window
       // column, so that a store's lanes write runs of ws scores ----
+      bool bad = false;
       for (int e = tid; e < qn * ws; e += NT) {
         const int j = e / ws, dw = e - j * ws;
         const int jh = j / tqw;
@@ -772,20 +710,23 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
           const double t0 = r0p[0], b0 = r0p[wp];
           const double top = fma((double)aw, (double)r0p[1], (1.0 - aw) * t0);
           const double bot = fma((double)aw, (double)r0p[wp + 1], (1.0 - aw) * b0);
-          const float dv = (float)(fma((double)ah, bot, (1.0 - ah) * top) * back);
-          srow[dh * ws] = ok && dv == dv ? dv : -INFINITY;  // NaN scores as invalid
+          const float dv = (float)fma((double)ah, bot, (1.0 - ah) * top);
+          const bool fin = fabsf(dv) < INFINITY;
+          srow[dh * ws] = ok && fin ? dv : -INFINITY;
+          bad = bad || (ok && !fin);
         }
       }
+      if (bad) *nonfin = fi + 1;
     } else if (fi + 1 < nfr) {
       set_queries(fi + 1);
     }
-    // an infinity in either image: its parts' products mix signs and zeros
-    // (inf x lo), so scores that are not finite are formed again from q and k
-    const bool again = tabled;
-    if (!again || __float_as_uint(kuni) == 0x80000000u || __float_as_uint(quni) == 0x80000000u) {
-      if (again) __syncthreads();  // the frame's scores are written
-      // or a union that costs more to sweep: this frame's candidates one by
-      // one (inner products for both distances, as the top-k pass expects)
+    // One by one: all candidates of a union that costs more to sweep, or those
+    // valid ones whose score came out infinite or NaN (the parts' products of an
+    // infinity mix signs and zeros, partial sums may overflow where the score
+    // does not, and a NaN key outside the patch's pixels meets q's zeros there).
+    // Inner products for both distances, as the top-k pass expects.
+    if (tabled) __syncthreads();  // the frame's scores are written, the tables free, the next frame's queries set
+    if (!tabled || *nonfin == fi + 1) {
       Geo gp = g;
       gp.dist = SNLS_DIST_PROD;
       for (int e = tid; e < qn * ws; e += NT) {
@@ -799,33 +740,31 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
         for (int dw = 0; dw < ws; ++dw) {
           const float disp_w = cand_disp(F.y, g.s1, dw, r);
           float* const at = scores + ((rowb + mh) * g.nW + mw) * pitch + cbase + dh * ws + dw;
-          if (again && fabsf(*at) < INFINITY) continue;
+          if (tabled && *at > -INFINITY) continue;
           float d = -INFINITY;
           if (okh && centre_ok(w, disp_w, g.W)) d = score_candidate(q, k, gp, b, hd, t, h, w, t2, disp_h, disp_w);
           *at = d;
         }
       }
+      if (!tabled) __syncthreads();  // the next frame's queries are set
     }
-    __syncthreads();  // the tables are free, the next frame's queries set
   }
 }
 
 // Tile geometry for tqh query rows; false when the LDS of one CU cannot hold it.
 static bool mf_geo(const Geo& g, int tqh, MfGeo* m) {
   m->nc32 = mf_chunks(g);
-  m->rec = m->nc32 * 128;
+  m->rec = m->nc32 * mf::CHUNK;
   m->tqw = (mf::HC - g.ps) / g.s0 + 1;
   m->tqh = tqh;
   m->hr = (tqh - 1) * g.s0 + g.ps;
   m->tiles_x = (g.nW + m->tqw - 1) / m->tqw;
   m->tiles_y = (g.nH + tqh - 1) / tqh;
-  m->qpitch = (m->nc32 > 1 ? 2 : 1) * 128 + 16;  // an odd number of 16-byte slots: consecutive pixels on different banks
+  m->qpitch = (m->nc32 > 1 ? 2 : 1) * mf::CHUNK + 16;  // an odd number of 16-byte slots: consecutive pixels on different banks
   m->wp = g.ws + 2;
   m->win = m->wp * m->wp;
   const long long qn = (long long)m->tqh * m->tqw;
   long long o = (long long)m->hr * mf::HC * m->qpitch;
-  m->o_qs = (int)o;
-  o += (long long)m->hr * mf::HC * 4;
   m->o_d = (int)o;
   o += (long long)mf::waves(m->nc32 > 1 ? 2 : 1) * mf::DBUF * 4;
   m->o_qi = (int)o;
@@ -837,7 +776,7 @@ static bool mf_geo(const Geo& g, int tqh, MfGeo* m) {
   m->o_dump = (int)o;
   o += 64 * 4;
   m->o_uni = (int)o;
-  o += (2 * g.wt + 1) * 16;
+  o += (2 * g.wt + 1) * 16 + 16;
   m->o_tab = (int)o;
   o += qn * m->win * 4;
   return o <= mf::LDS_BYTES;
@@ -868,24 +807,20 @@ static bool mf_tile(const Geo& g, MfGeo* best) {
 bool mfma_supported(const Geo& g) {
   if (!tile_supported(g) || g.Ch < 8) return false;
   // 32-bit byte offsets inside one frame's split plane
-  if ((long long)mf_chunks(g) * 128 * g.HW >= (1LL << 31)) return false;
+  if ((long long)mf_chunks(g) * mf::CHUNK * g.HW >= (1LL << 31)) return false;
   MfGeo m;
   if (!mf_tile(g, &m)) return false;
   return (long long)g.B * g.T * g.HD <= 65535 &&
          (long long)m.tiles_x * m.tiles_y * g.B * g.HD * g.T <= 0x7fffffffLL;
 }
 
-static size_t mf_align(size_t b) { return (b + 255) & ~(size_t)255; }
-static size_t mf_plane_bytes(const Geo& g) { return mf_align((size_t)g.B * g.T * g.HD * (size_t)g.HW * mf_chunks(g) * 128); }
-static size_t mf_scale_bytes(const Geo& g) { return mf_align((size_t)g.B * g.T * g.HD * (size_t)g.HW * 4); }
-
-// Per image: its statistics and its scale.
-static size_t mf_info_bytes(const Geo& g) {
-  return mf_align((size_t)g.B * g.T * g.HD * (kStatBlocks * sizeof(float2) + sizeof(float)));
+// Split copy of a video.
+static size_t mf_plane_bytes(const Geo& g) {
+  return ((size_t)g.B * g.T * g.HD * (size_t)g.HW * mf_chunks(g) * mf::CHUNK + 255) & ~(size_t)255;
 }
 
-// Split copies and scales of q and k.
-size_t mfma_ws_bytes(const Geo& g) { return 2 * (mf_plane_bytes(g) + mf_scale_bytes(g) + mf_info_bytes(g)); }
+// Split copies of q and k.
+size_t mfma_ws_bytes(const Geo& g) { return 2 * mf_plane_bytes(g); }
 
 snls_status launch_mfma_scores(const float* q, const float* k, const float* flows, const Geo& g, float* scores,
                                int pitch, void* ws, hipStream_t s) {
@@ -893,36 +828,16 @@ snls_status launch_mfma_scores(const float* q, const float* k, const float* flow
   if (!mf_tile(g, &m)) return SNLS_ERR_UNSUPPORTED;
   const long long nwg = (long long)m.tiles_x * m.tiles_y * g.B * g.HD * g.T;
   if (nwg == 0) return SNLS_OK;
-  struct Split {
-    unsigned char* planes;
-    float *scale, *info;
-  };
-  unsigned char* at = static_cast<unsigned char*>(ws);
-  const unsigned nslab = (unsigned)(g.B * g.T * g.HD);
-  auto split = [&](const float* x) {
-    Split r;
-    r.planes = at;
-    at += mf_plane_bytes(g);
-    r.scale = reinterpret_cast<float*>(at);
-    at += mf_scale_bytes(g);
-    float2* stats = reinterpret_cast<float2*>(at);
-    r.info = reinterpret_cast<float*>(stats + (size_t)nslab * kStatBlocks);
-    at += mf_info_bytes(g);
-    const unsigned nblk = (unsigned)((g.HW + 63) / 64);
-    const unsigned nst = (unsigned)((g.HW + 255) / 256);
-    const unsigned nstat = nst < (unsigned)kStatBlocks ? nst : (unsigned)kStatBlocks;
-    hipLaunchKernelGGL(mf_stats_kernel, dim3(nstat, nslab), dim3(256), 0, s, x, g, stats);
-    hipLaunchKernelGGL(mf_split_kernel, dim3(nblk, nslab), dim3(256), 0, s, x, g, m.nc32, stats, (int)nstat, r.planes,
-                       r.scale, r.info);
-    return r;
-  };
-  const Split ksp = split(k);
-  const Split qsp = q == k ? ksp : split(q);  // one video matched with itself: one copy serves both
+  const unsigned nslab = (unsigned)(g.B * g.T * g.HD), nblk = (unsigned)((g.HW + 63) / 64);
+  unsigned char* const ks = static_cast<unsigned char*>(ws);
+  unsigned char* const qs = q == k ? ks : ks + mf_plane_bytes(g);  // one video matched with itself: one copy serves both
+  hipLaunchKernelGGL(mf_split_kernel, dim3(nblk, nslab), dim3(256), 0, s, k, g, m.nc32, ks);
+  if (q != k) hipLaunchKernelGGL(mf_split_kernel, dim3(nblk, nslab), dim3(256), 0, s, q, g, m.nc32, qs);
   const dim3 grid((unsigned)nwg), block(mf::waves(m.nc32 > 1 ? 2 : 1) * 64);
   switch (4 * g.ps + (m.nc32 > 1 ? 2 : 0) + (g.s0 == 1 ? 1 : 0)) {
 #define SNLS_MF_LAUNCH(P, C, S)                                                                                    \
-  hipLaunchKernelGGL((search_mfma_scores_kernel<P, C, S>), grid, block, 0, s, q, k, qsp.planes, qsp.scale,   \
-                     qsp.info, ksp.planes, ksp.scale, ksp.info, flows, g, m, scores, pitch);                                                                               \
+  hipLaunchKernelGGL((search_mfma_scores_kernel<P, C, S>), grid, block, 0, s, q, k, qs, ks, flows, g, m, scores, \
+                     pitch);                                                                                       \
   break
 #define SNLS_MF_CASE(P)                         \
   case 4 * P: SNLS_MF_LAUNCH(P, 1, false);      \

@@ -2,8 +2,8 @@
 kernel changes path: channel padding and chunk groups (8 to 130 channels per
 head), unions of shift columns at the edges of two and three key blocks and of
 the three lane layouts (17/18, 21/22, 32/33 columns) and of several sweeps, more
-shift rows than one round holds, strided queries, every patch size, and images whose pixels need
-scales of their own."""
+shift rows than one round holds, strided queries, every patch size, pixels and
+channels of very different size, and values that are not finite."""
 import numpy as np
 import pytest
 import torch
@@ -113,7 +113,7 @@ def test_tall_frames(dev, H, s0):
 def test_pixels_with_scales_of_their_own(dev, which):
     """Pixels from 1e-12 to 1e12 in one image: each score is compared with
     the largest score its own row could have, so that a lost low-magnitude
-    pixel would show (22-bit operands: 1e-6 of the row's scale)."""
+    pixel would show (seven roundings of sums of at most that size: 4.2e-7)."""
     p = small_params(T=2, C=24, H=30, W=33, ws=5, wt=1, ps=1, k=33)
     rng = np.random.default_rng(77)
     shp = (1, 2, 24, 30, 33)
@@ -139,7 +139,99 @@ def test_pixels_with_scales_of_their_own(dev, which):
     Y = np.clip(y[None, :, :, None] + at[..., 1], 0, 29).astype(int)
     X = np.clip(x[None, :, :, None] + at[..., 2], 0, 32).astype(int)
     bound = qn[:, None] * kn[np.clip(f, 0, 1), Y, X].reshape(-1, 33)
-    assert (err <= 1e-6 * bound + 1e-30)[fin].all()
+    assert (err <= 4.2e-7 * bound + 1e-30)[fin].all()
+
+
+def _exact_scores(q, k, ps, ws):
+    """64-bit scores (H, W, ws * ws) of one frame matched with itself at whole shifts, -inf outside the frame."""
+    C, H, W = q.shape
+    r, lo, m = ws // 2, ps // 2, ws + ps
+    kp = np.pad(k.astype(np.float64), ((0, 0), (m, m), (m, m)))
+    out = np.full((H, W, ws * ws), -np.inf)
+    y, x = np.mgrid[0:H, 0:W]
+    for d in range(ws * ws):
+        dy, dx = d // ws - r, d % ws - r
+        pr = np.pad((q.astype(np.float64) * kp[:, m + dy:m + dy + H, m + dx:m + dx + W]).sum(0), m)
+        box = sum(pr[m - lo + a:m - lo + a + H, m - lo + b:m - lo + b + W] for a in range(ps) for b in range(ps))
+        ok = (y + dy >= 0) & (y + dy < H) & (x + dx >= 0) & (x + dx < W)
+        out[..., d] = np.where(ok, box, -np.inf)
+    return out
+
+
+@pytest.mark.parametrize("ps,C,ws", [(3, 32, 5), (1, 32, 3), (7, 64, 5), (3, 160, 5)])
+@pytest.mark.parametrize("kind", ["spread", "apart", "noise"])
+@pytest.mark.parametrize("bits", [0, 16, 20, 30])
+def test_error_no_larger_than_the_vector_units(dev, ps, C, ws, kind, bits):
+    """Channels of q and k up to 2^bits apart (spread: falling in q, rising in
+    k; apart: each has its own large channel, which the other lacks): the
+    scores' error against 64 bits is no larger than that of the fp32 kernel,
+    which a search that keeps every candidate runs (5% for chance)."""
+    if kind == "noise" and bits:
+        pytest.skip("noise has channels of one size")
+    n = ws * ws
+    p = small_params(T=1, C=C, H=48, W=56, ws=ws, wt=0, ps=ps, k=n)
+    rng = np.random.default_rng(C + bits)
+    q = rng.standard_normal((C, 48, 56))
+    k = q + 0.3 * rng.standard_normal(q.shape) if kind != "noise" else rng.standard_normal(q.shape)
+    if kind == "spread":
+        s = 2.0 ** (-bits * np.arange(C) / (C - 1))
+        q, k = q * s[:, None, None], k * s[::-1, None, None]
+    elif kind == "apart":
+        q[2:] *= 2.0 ** -bits
+        k[2:] *= 2.0 ** -bits
+        q[1] = k[0] = 0
+    q, k = q.astype(np.float32), k.astype(np.float32)
+    ref = _exact_scores(q, k, ps, ws)
+    fl = np.zeros((1, 1, 0, 2, 48, 56), np.float32)
+    gd, gi = _search(q[None, None], k[None, None], fl, p, dev)
+    ad, _ = B.snls_search(torch.from_numpy(q[None, None]).to(dev), torch.from_numpy(k[None, None]).to(dev),
+                          torch.from_numpy(fl).to(dev), dict(p, k=0))
+    at = ((gi[..., 1] + ws // 2) * ws + gi[..., 2] + ws // 2).astype(int)
+    ref = ref.reshape(-1, n)
+    gref = np.take_along_axis(ref, at, 1)
+    ad = ad.cpu().numpy().reshape(-1, n)
+    fin = np.isfinite(ref)
+    assert np.array_equal(np.isfinite(gd), np.isfinite(gref)) and np.array_equal(np.isfinite(ad), fin)
+    rel = lambda a, b, m: np.linalg.norm(a[m].astype(np.float64) - b[m]) / np.linalg.norm(b[m])
+    here, vector = rel(gd, gref, np.isfinite(gref)), rel(ad, ref, fin)
+    assert here <= 1.05 * vector, (here, vector)
+
+
+@pytest.mark.parametrize("ps,C", [(1, 32), (3, 16), (7, 48), (3, 140)])
+@pytest.mark.parametrize("what", ["nan", "inf", "huge"])
+def test_values_that_are_not_finite_or_overflow(dev, ps, C, what):
+    """NaN and infinite features and ones that bf16 rounds to infinity,
+    anywhere in the frame: a candidate is invalid when a pixel of its patch
+    inside the frame gives NaN, and not for keys that only pixels outside it
+    meet.  The keys' ones are in frame 1 and the queries compared in frame 0,
+    half offsets away (no tap has weight 0)."""
+    p = small_params(T=2, C=C, H=34, W=36, ws=5, wt=1, ps=ps, k=16)
+    rng = np.random.default_rng(C)
+    shp = (1, 2, C, 34, 36)
+    q, k = (rng.standard_normal(shp, dtype=np.float32) for _ in range(2))
+    big = {"nan": [np.nan], "inf": [np.inf, -np.inf], "huge": [3.4028e38, -3.4e38]}[what]
+    if what == "huge":
+        k *= 1e-3
+    for a in (q,) if what == "huge" else (q, k):
+        f = 0 if a is q else 1
+        for _ in range(8):
+            a[0, f, rng.integers(0, C), rng.integers(0, 34), rng.integers(0, 36)] = rng.choice(big)
+        a[0, f, 3, 0, 5] = a[0, f, 5, 33, 35] = a[0, f, 1, 12, 0] = a[0, f, 2, 20, 35] = big[0]
+    fl = (rng.integers(-3, 3, (1, 2, 2, 2, 34, 36)) + 0.5).astype(np.float32)
+    gd, gi = _search(q, k, fl, p, dev)
+    n = 34 * 36
+    gd, ref = gd[:n], oracle.search(q, k, fl, p)["dists"][:n, :p["k"]]
+    assert not np.isnan(gd).any()
+    for inf in (np.inf, -np.inf):
+        assert np.array_equal((gd == inf).sum(1), (ref == inf).sum(1))
+    fin = np.isfinite(ref)
+    scale = np.maximum(np.abs(ref), 4 * ps * ps * np.sqrt(C))
+    if what == "huge":  # products that cancel: the size of the patch's largest ones
+        m = np.pad(np.abs(q[0, 0].astype(np.float64)).sum(0), ps)
+        lo = ps - ps // 2
+        box = sum(m[lo + a:lo + a + 34, lo + b:lo + b + 36] for a in range(ps) for b in range(ps))
+        scale = np.broadcast_to(box.reshape(-1, 1) * np.abs(k).max(), ref.shape)
+    assert (np.abs(gd[fin].astype(np.float64) - ref[fin]) <= 1e-5 * scale[fin]).all()
 
 
 @pytest.mark.parametrize("ps", [1, 3, 7])

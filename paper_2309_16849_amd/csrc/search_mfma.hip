@@ -481,7 +481,8 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
   int2* const qi = reinterpret_cast<int2*>(smem + mg.o_qi);
   int2* const ql = reinterpret_cast<int2*>(smem + mg.o_ql);  // a query's first shift row and column
   float* const dump = reinterpret_cast<float*>(smem + mg.o_dump);
-  // min N_h, max N_h, min N_w, max N_w of each frame; the last frame step (from 1) with a score that is not finite
+  // min N_h, max N_h, min N_w, max N_w of each frame; the last frame step (from 1) with an infinite or NaN
+  // score, and with an infinity in its reach
   int* const uni = reinterpret_cast<int*>(smem + mg.o_uni);
   int* const nonfin = uni + 4 * (2 * g.wt + 1);
 
@@ -515,7 +516,7 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
   auto slab = [&](int tt) { return ((long long)b * g.T + tt) * g.HD + hd; };
 
   // ---- the halo of q (split records), the tile's offsets ----
-  if (tid == 0) *nonfin = 0;
+  if (tid < 2) nonfin[tid] = 0;
   for (int e = tid; e < nfr * qn; e += NT) {
     const int fi = e / qn, j = e - fi * qn, dt = dt0 + fi;
     const int h = y0 + s0 * (j / tqw), w = x0 + s0 * (j % tqw);
@@ -711,22 +712,16 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
           const double top = fma((double)aw, (double)r0p[1], (1.0 - aw) * t0);
           const double bot = fma((double)aw, (double)r0p[wp + 1], (1.0 - aw) * b0);
           const float dv = (float)fma((double)ah, bot, (1.0 - ah) * top);
-          const bool fin = fabsf(dv) < INFINITY;
-          srow[dh * ws] = ok && fin ? dv : -INFINITY;
-          bad = bad || (ok && !fin);
+          srow[dh * ws] = ok && dv == dv ? dv : -INFINITY;  // NaN scores as invalid
+          bad = bad || (ok && !(fabsf(dv) < INFINITY));
         }
       }
-      if (bad) *nonfin = fi + 1;
+      if (bad) nonfin[0] = fi + 1;
     } else if (fi + 1 < nfr) {
       set_queries(fi + 1);
     }
-    // One by one: all candidates of a union that costs more to sweep, or those
-    // valid ones whose score came out infinite or NaN (the parts' products of an
-    // infinity mix signs and zeros, partial sums may overflow where the score
-    // does not, and a NaN key outside the patch's pixels meets q's zeros there).
-    // Inner products for both distances, as the top-k pass expects.
-    if (tabled) __syncthreads();  // the frame's scores are written, the tables free, the next frame's queries set
-    if (!tabled || *nonfin == fi + 1) {
+    if (!tabled) {  // the frame's candidates one by one
+      // (inner products for both distances, as the top-k pass expects)
       Geo gp = g;
       gp.dist = SNLS_DIST_PROD;
       for (int e = tid; e < qn * ws; e += NT) {
@@ -739,14 +734,83 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
         const bool okh = centre_ok(h, disp_h, g.H);
         for (int dw = 0; dw < ws; ++dw) {
           const float disp_w = cand_disp(F.y, g.s1, dw, r);
-          float* const at = scores + ((rowb + mh) * g.nW + mw) * pitch + cbase + dh * ws + dw;
-          if (tabled && *at > -INFINITY) continue;
           float d = -INFINITY;
           if (okh && centre_ok(w, disp_w, g.W)) d = score_candidate(q, k, gp, b, hd, t, h, w, t2, disp_h, disp_w);
-          *at = d;
+          scores[((rowb + mh) * g.nW + mw) * pitch + cbase + dh * ws + dw] = d;
         }
       }
-      if (!tabled) __syncthreads();  // the next frame's queries are set
+    }
+    __syncthreads();  // the tables are free, the next frame's queries set, the frame's scores written
+    if (tabled && nonfin[0] == fi + 1) {
+      // Scores that are infinite or NaN.  The products of an infinity's parts mix
+      // signs and zeros: with one in reach these scores are formed again from q and
+      // k.  Without, a NaN comes from a NaN -- of the patch, or, for patches that
+      // stick out of the frame, from keys that only q's zeros there meet: only
+      // those are formed again.
+      int tidr = tid;  // (index arithmetic done here, not kept live across the frames)
+      asm volatile("" : "+v"(tidr));
+      const int laner = tidr & 63;
+      bool infs = false;
+      auto look = [&](const unsigned char* plane, int y0_, int ny, int x0_, int nx) {
+        const int npc = mg.nc32 * 4, n = ny * nx * npc;
+        for (int e = tidr; e < n; e += NT) {
+          const int pc = e / (ny * nx), p = e - pc * (ny * nx);
+          const int gy = y0_ + p / nx, gx = x0_ + p % nx;
+          if (gy < 0 || gy >= g.H || gx < 0 || gx >= g.W) continue;
+          const u32x4 v = *reinterpret_cast<const u32x4*>(
+              plane + (long long)gy * g.W * rec + ((long long)((pc >> 2) * (4 * PARTS) + (pc & 3)) * g.W + gx) * 16);
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            infs = infs || (v[i] & 0x7fffu) == 0x7f80u || (v[i] & 0x7fff0000u) == 0x7f800000u;
+        }
+      };
+      look(qs + slab(t) * g.HW * rec, Y0, hr, X0, HC);
+      look(ks + slab(t2) * g.HW * rec, Y0 + dmin_h, hr + UH - 1, X0 + dmin_w, HC + UW - 1);
+      if (infs) nonfin[1] = fi + 1;
+      __syncthreads();
+      infs = nonfin[1] == fi + 1;
+      const int ncell = ws * ws, nterm = PS * PS * g.Ch;
+      const float* const qbase = q + (((long long)b * g.T + t) * g.C + (long long)hd * g.Ch) * g.HW;
+      const float* const kbase = k + (((long long)b * g.T + t2) * g.C + (long long)hd * g.Ch) * g.HW;
+      // a lane finds a candidate, the wave forms its score
+      for (int e0 = tidr - laner; e0 < qn * ncell; e0 += NT) {
+        const int e = e0 + laner;
+        const int j = e / ncell, cell = e - j * ncell;
+        const int mh = my0 + j / tqw, mw = mx0 + j % tqw;
+        const int h = mh * s0, w = mw * s0;
+        float dh_ = 0.f, dw_ = 0.f;
+        float* at = nullptr;
+        bool todo = e < qn * ncell && mh < g.nH && mw < g.nW;
+        if (todo) {
+          dh_ = cand_disp(ff[j].x, g.s1, cell / ws, r);
+          dw_ = cand_disp(ff[j].y, g.s1, cell % ws, r);
+          at = scores + ((rowb + mh) * g.nW + mw) * pitch + cbase + cell;
+          const bool out = h + LO < 0 || h + LO + PS > g.H || w + LO < 0 || w + LO + PS > g.W;
+          todo = (infs || out) && centre_ok(h, dh_, g.H) && centre_ok(w, dw_, g.W) && !(fabsf(*at) < INFINITY);
+        }
+        unsigned long long m = __ballot(todo);
+        while (m) {
+          const int src = __ffsll((long long)m) - 1;
+          m &= m - 1;
+          const int ch = __shfl(h, src), cw = __shfl(w, src);
+          int nh, nw;
+          float ah, aw;
+          split_disp(__shfl(dh_, src), &nh, &ah);
+          split_disp(__shfl(dw_, src), &nw, &aw);
+          float sum = 0.f;
+          for (int i0 = 0; i0 < nterm; i0 += 64) {
+            const int i = i0 + laner, c = i / (PS * PS), pp = i - c * (PS * PS);
+            const int y = ch + LO + pp / PS, x = cw + LO + pp % PS;
+            if (i < nterm && y >= 0 && y < g.H && x >= 0 && x < g.W)
+              sum = fmaf(qbase[c * g.HW + (long long)y * g.W + x],
+                         bilinear_plane(kbase + c * g.HW, g.H, g.W, y + nh, x + nw, ah, aw), sum);
+            if (__any(sum != sum)) break;
+          }
+#pragma unroll
+          for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+          if (laner == src) *at = sum == sum ? sum : -INFINITY;
+        }
+      }
     }
   }
 }

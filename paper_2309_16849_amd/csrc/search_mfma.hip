@@ -867,9 +867,13 @@ static bool mf_tile(const Geo& g, MfGeo* best) {
 }
 
 // Heads of 8 channels or more: fewer would be padded to 32 (the contraction is
-// then mostly zeros; 2 x 4-channel heads keep the vector-unit kernel).
+// then mostly zeros; 2 x 4-channel heads keep the vector-unit kernel).  At P = 7
+// and S_Q > 1, where most of the box sums are not a query's, 16 or more (160x160,
+// T = 5, Ws = 9, S_Q = 2: 8 channels 0.64 ms here, 0.52 on the vector units, 12
+// channels 0.65 and 0.57; at S_Q = 1 8 channels 0.67 and 0.64, with Ws = 5 at
+// half-pixel steps 0.43 and 0.61).
 bool mfma_supported(const Geo& g) {
-  if (!tile_supported(g) || g.Ch < 8) return false;
+  if (!tile_supported(g) || g.Ch < (g.ps == 7 && g.s0 > 1 ? 16 : 8)) return false;
   // 32-bit byte offsets inside one frame's split plane
   if ((long long)mf_chunks(g) * mf::CHUNK * g.HW >= (1LL << 31)) return false;
   MfGeo m;

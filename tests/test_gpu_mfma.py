@@ -44,7 +44,8 @@ def _search(q, k, fl, p, dev):
 CASES = [  # patch, channels, heads, window, query stride, key stride, spread of rows and columns
     (7, 8, 1, 9, 1, 1.0, 4, 7), (7, 64, 1, 9, 1, 1.0, 6, 8), (7, 65, 1, 9, 1, 1.0, 14, 11), (3, 33, 1, 9, 1, 1.0, 7, 12),
     (5, 130, 1, 5, 1, 0.5, 3, 18), (7, 96, 3, 9, 1, 1.0, 26, 22), (1, 32, 1, 9, 1, 0.5, 5, 27), (2, 24, 2, 7, 1, 1.0, 9, 24),
-    (4, 16, 1, 8, 2, 1.0, 8, 11), (6, 40, 1, 9, 3, 0.75, 5, 6), (7, 16, 1, 15, 1, 1.0, 3, 3), (7, 72, 1, 13, 2, 1.0, 9, 19),
+    (4, 16, 1, 8, 2, 1.0, 8, 11), (6, 40, 1, 9, 3, 0.75, 5, 6), (7, 16, 1, 15, 1, 1.0, 3, 3), (7, 72, 1, 13, 2, 1.0, 9, 19), (7, 15, 1, 9, 2, 1.0, 5, 6),
+    (7, 16, 1, 9, 2, 1.0, 5, 6),
 ]
 
 

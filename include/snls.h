@@ -121,24 +121,27 @@ typedef struct {
  *                            inds  (B, HD, T, nH, nW, k, 3)
  *   p->k == 0 every candidate in id order (invalid ones at -inf / +inf):
  *             dists (B, HD, T, nH, nW, (2wt+1)*ws*ws), inds (..., 3)
- *   workspace device scratch of at least snls_workspace_size(SNLS_OP_SEARCH, p)
- *             bytes, 256-byte aligned; may be NULL when that size is 0.  The
- *             tiled top-k path (ps <= 7 with ws <= 9, or ps = 7 with ws <=
- *             15; stride1 <= 1; any stride0) and the single-pixel path with
+ *   workspace device scratch of snls_workspace_size(SNLS_OP_SEARCH, p) bytes,
+ *             256-byte aligned; may be NULL when that size is 0.  The tiled
+ *             top-k path (ps <= 7 with ws <= 9, or ps = 7 with ws <= 15;
+ *             stride1 <= 1; any stride0) and the single-pixel path with
  *             k > 32 (ps = 1, stride1 = 1, ws <= 15, inner product) score
  *             every candidate into it (4 bytes per query row and candidate,
- *             rows padded to 32 candidates) before selecting, and with 8 or
- *             more channels per head also holds copies of q and k split for
- *             the matrix cores (each 4 bytes per element, channels per head
- *             padded to 32 or a multiple of 64); squared L2
+ *             rows padded to 32 candidates) before selecting; squared L2
  *             adds the key-norm term of every candidate, the query norm of
  *             every row, five key pair products per key pixel, frame and
  *             head, the squared norm of every query pixel per frame and head
  *             and, where the norm terms are formed cell by cell (stride1 < 1
  *             or ws > 9), fp64 summed-area tables of the five products.  The
- *             fused single-pixel path (k <= 32; not at stride0 = 1
- *             with 32 or more channels per head and k <= 16) needs none.  Its contents
- *             are not needed between calls
+ *             fused single-pixel path (k <= 32) needs none.  Its contents
+ *             are not needed between calls.
+ *             With 8 or more channels per head the size also holds copies of
+ *             q and k split for the matrix cores (each 6 bytes per element,
+ *             channels per head padded to 32 or a multiple of 64), which come
+ *             last.  A workspace without room for them, as described above
+ *             (none for ps = 1 with k <= 32), is accepted too: the search
+ *             then runs on the vector units, with the same rounding rules and
+ *             more time
  * Errors: SNLS_ERR_INVALID_ARG for shapes/parameters out of range or NULL
  * buffers; SNLS_ERR_UNSUPPORTED for k > SNLS_MAX_K; SNLS_ERR_WORKSPACE for a
  * missing, short or misaligned workspace; SNLS_ERR_HIP on a launch failure. */

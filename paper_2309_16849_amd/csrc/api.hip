@@ -23,11 +23,13 @@ snls_status device_ready() {
   return SNLS_OK;
 }
 
-// Only the scored top-k paths need scratch: the scores of every candidate.
-size_t search_ws_bytes(const Geo& g) {
+// Only the scored top-k paths use scratch: the scores of every candidate, and
+// the split copies of the matrix cores' operands.  have: the bytes at hand.
+size_t search_ws_bytes(const Geo& g, size_t have) {
   if (g.k < 1) return 0;
-  const SearchRoute r = search_route(g);
-  return r == SearchRoute::Tile || r == SearchRoute::P1Scored ? tile_ws_bytes(g) : 0;
+  const SearchRoute r = search_route(g, have);
+  if (r == SearchRoute::Tile) return tile_ws_bytes(g);
+  return r == SearchRoute::TileVector || r == SearchRoute::P1Scored ? tile_base_bytes(g) : 0;
 }
 
 }  // namespace
@@ -50,7 +52,7 @@ const char* snls_status_string(snls_status s) {
 
 size_t snls_workspace_size(int op, const snls_params* p) {
   Geo g;
-  if (op == SNLS_OP_SEARCH) return check_params(p, false, &g) == SNLS_OK ? search_ws_bytes(g) : (size_t)-1;
+  if (op == SNLS_OP_SEARCH) return check_params(p, false, &g) == SNLS_OK ? search_ws_bytes(g, (size_t)-1) : (size_t)-1;
   if (op == SNLS_OP_AGGREGATE) return check_params(p, true, &g) == SNLS_OK ? aggregate_ws_bytes(g) : (size_t)-1;
   if (op == SNLS_OP_BACKWARD) return check_params(p, true, &g) == SNLS_OK ? backward_ws_bytes(g) : (size_t)-1;
   if (op == SNLS_OP_AGGREGATE_STACKED)
@@ -107,12 +109,12 @@ snls_status snls_search(const float* q, const float* k, const float* flows, cons
   snls_status st = check_params(p, false, &g);
   if (st != SNLS_OK) return st;
   if (!q || !k || !dists || !inds || (g.wt > 0 && !flows)) return SNLS_ERR_INVALID_ARG;
-  const size_t need = search_ws_bytes(g);
-  if (need > 0 && (!workspace || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255)))
-    return SNLS_ERR_WORKSPACE;
+  // (short of the full size: what the route without the split copies needs)
+  const size_t have = workspace && !(reinterpret_cast<uintptr_t>(workspace) & 255) ? workspace_bytes : 0;
+  if (have < search_ws_bytes(g, have)) return SNLS_ERR_WORKSPACE;
   if ((st = device_ready()) != SNLS_OK) return st;
   if (g.k == 0) return launch_search_full(q, k, flows, g, dists, inds, as_stream(stream));
-  return launch_search_topk(q, k, flows, g, dists, inds, workspace, as_stream(stream));
+  return launch_search_topk(q, k, flows, g, dists, inds, workspace, have, as_stream(stream));
 }
 
 snls_status snls_topk(const float* dists_all, const float* inds_all, int64_t rows, int32_t n_cand, int32_t k,

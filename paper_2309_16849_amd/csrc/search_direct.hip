@@ -192,7 +192,11 @@ snls_status launch_search_topk_direct(const float* q, const float* k, const floa
   return hipGetLastError() == hipSuccess ? SNLS_OK : SNLS_ERR_HIP;
 }
 
-SearchRoute search_route(const Geo& g) {
+SearchRoute search_route(const Geo& g, size_t have) {
+  // The matrix cores, where the workspace has room for their operands: a
+  // search with the scores' part alone, or none for single pixels, takes the
+  // route without them.
+  const bool matrix = tile_supported(g) && mfma_supported(g) && have >= tile_ws_bytes(g);
   // Single-pixel patches have no overlap for the tiles to share, but the
   // matrix cores still pay where the head has 32 channels or more and every
   // pixel is a query (k <= 16: the 16-lane top-k).  Fused kernel against the
@@ -202,21 +206,23 @@ SearchRoute search_route(const Geo& g) {
   // per-query kernel (k <= 32) takes the other single-pixel searches and needs
   // no score workspace; the scored single-pixel route only at a query stride
   // above 1.
-  if (g.ps == 1 && g.s0 == 1 && g.Ch >= 32 && g.k <= 16 && tile_supported(g) && mfma_supported(g))
-    return SearchRoute::Tile;
+  if (g.ps == 1 && g.s0 == 1 && g.Ch >= 32 && g.k <= 16 && matrix) return SearchRoute::Tile;
   if (g.ps == 1 && p1_fused(g)) return SearchRoute::P1Fused;
   if (g.ps == 1 && g.s0 > 1 && p1_supported(g)) return SearchRoute::P1Scored;
-  if (tile_supported(g)) return SearchRoute::Tile;
+  if (tile_supported(g)) return matrix ? SearchRoute::Tile : SearchRoute::TileVector;
   if (p1_supported(g)) return p1_fused(g) ? SearchRoute::P1Fused : SearchRoute::P1Scored;
   return SearchRoute::Direct;
 }
 
 snls_status launch_search_topk(const float* q, const float* k, const float* flows, const Geo& g, float* dists,
-                               float* inds, void* ws, hipStream_t s) {
-  switch (search_route(g)) {
+                               float* inds, void* ws, size_t have, hipStream_t s) {
+  const SearchRoute route = search_route(g, have);
+  switch (route) {
     case SearchRoute::P1Fused: return launch_search_p1_topk(q, k, flows, g, dists, inds, s);
     case SearchRoute::P1Scored: return launch_search_p1(q, k, flows, g, dists, inds, static_cast<float*>(ws), s);
-    case SearchRoute::Tile: return launch_search_tile(q, k, flows, g, dists, inds, static_cast<float*>(ws), s);
+    case SearchRoute::Tile:
+    case SearchRoute::TileVector:
+      return launch_search_tile(q, k, flows, g, dists, inds, static_cast<float*>(ws), route == SearchRoute::Tile, s);
     default: return launch_search_topk_direct(q, k, flows, g, dists, inds, s);
   }
 }

@@ -1151,7 +1151,7 @@ static size_t tile_plane_bytes(const Geo& g) {
   return ((size_t)g.rows * (size_t)tile_ws_pitch(g) * sizeof(float) + 255) & ~(size_t)255;
 }
 // The split copies of the matrix-core scores come last.
-static size_t tile_base_bytes(const Geo& g) {
+size_t tile_base_bytes(const Geo& g) {
   size_t b = tile_plane_bytes(g);                             // inner-product scores
   if (g.dist == SNLS_DIST_L2)  // key and query norm terms, key pair planes
     b += tile_plane_bytes(g) + (((size_t)g.rows * sizeof(float) + 255) & ~(size_t)255) + l2_planes_bytes(g);
@@ -1259,9 +1259,9 @@ snls_status launch_tile_scores(const float* q, const float* k, const float* flow
 }
 
 snls_status launch_search_tile(const float* q, const float* k, const float* flows, const Geo& g, float* dists,
-                               float* inds, float* scores, hipStream_t s) {
+                               float* inds, float* scores, bool matrix, hipStream_t s) {
   const int pitch = tile_ws_pitch(g);
-  if (mfma_supported(g)) {
+  if (matrix) {
     const snls_status st = launch_mfma_scores(q, k, flows, g, scores, pitch,
                                               reinterpret_cast<char*>(scores) + tile_base_bytes(g), s);
     if (st != SNLS_OK) return st;

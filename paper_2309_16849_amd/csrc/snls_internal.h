@@ -62,9 +62,10 @@ size_t gather_ws_bytes(const Geo& g);
 // score of every candidate (rows x candidates fp32), plus for L2 the key-norm
 // term of every candidate and the query-norm term of every row.
 bool tile_supported(const Geo& g);
-size_t tile_ws_bytes(const Geo& g);
+size_t tile_base_bytes(const Geo& g);
 // The tiled route's scores on the matrix cores (8 channels per head or more)
-// and the split copies of q and k they read (part of tile_ws_bytes).
+// and the split copies of q and k they read; tile_ws_bytes: with these.
+size_t tile_ws_bytes(const Geo& g);
 bool mfma_supported(const Geo& g);
 size_t mfma_ws_bytes(const Geo& g);
 // Single-pixel patches (P = 1), any S_Q, S_K = 1, inner product, Ws <= 15:
@@ -73,9 +74,10 @@ size_t mfma_ws_bytes(const Geo& g);
 bool p1_supported(const Geo& g);
 bool p1_fused(const Geo& g);
 
-// Kernels a top-k search (k >= 1) runs on.
-enum class SearchRoute { Direct, Tile, P1Scored, P1Fused };
-SearchRoute search_route(const Geo& g);
+// Kernels a top-k search (k >= 1) with a workspace of `have` bytes runs on
+// (Tile: scores on the matrix cores, TileVector: on the vector units).
+enum class SearchRoute { Direct, Tile, TileVector, P1Scored, P1Fused };
+SearchRoute search_route(const Geo& g, size_t have);
 
 #ifdef __HIPCC__
 
@@ -83,11 +85,11 @@ SearchRoute search_route(const Geo& g);
 snls_status launch_search_full(const float* q, const float* k, const float* flows, const Geo& g, float* dists,
                                float* inds, hipStream_t s);
 snls_status launch_search_topk(const float* q, const float* k, const float* flows, const Geo& g, float* dists,
-                               float* inds, void* ws, hipStream_t s);
+                               float* inds, void* ws, size_t have, hipStream_t s);
 snls_status launch_search_topk_direct(const float* q, const float* k, const float* flows, const Geo& g,
                                       float* dists, float* inds, hipStream_t s);
 snls_status launch_search_tile(const float* q, const float* k, const float* flows, const Geo& g, float* dists,
-                               float* inds, float* scores, hipStream_t s);
+                               float* inds, float* scores, bool matrix, hipStream_t s);
 snls_status launch_search_p1(const float* q, const float* k, const float* flows, const Geo& g, float* dists,
                              float* inds, float* scores, hipStream_t s);
 snls_status launch_search_p1_scores(const float* q, const float* k, const float* flows, const Geo& g, float* scores,

@@ -263,3 +263,31 @@ def test_gather_and_reduce_validation(lib):
                                   None) == B.SNLS_ERR_WORKSPACE
     wide = _params(C=160, HD=2)  # 80 channels per head
     assert lib.snls_stacked_reduce(FAKE, FAKE, ctypes.byref(wide), 8, FAKE, None) == B.SNLS_ERR_UNSUPPORTED
+
+
+def test_search_accepts_a_workspace_without_the_split_copies(lib):
+    """What a search needed before the matrix cores is still accepted: nothing
+    for single pixels with k <= 32, the scores' part of the tiled route, and the
+    strided single-pixel route needs no more than that."""
+    BAD = (B.SNLS_ERR_WORKSPACE, B.SNLS_ERR_INVALID_ARG, B.SNLS_ERR_UNSUPPORTED)
+
+    def call(prm, ws, n):
+        return lib.snls_search(FAKE, FAKE, FAKE, ctypes.byref(prm), FAKE, FAKE, ws, n, None)
+
+    if torch.cuda.is_available():
+        pytest.skip("the pointers are not real")
+    size = lambda prm: lib.snls_workspace_size(B.SNLS_OP_SEARCH, ctypes.byref(prm))
+    p1 = _params(C=32, HD=1, ps=1, ws=9, k=10)
+    assert size(p1) > 0
+    for ws, n in ((None, 0), (None, BIG), (ctypes.c_void_p(256 * 4097 + 16), BIG), (FAKE, 64)):
+        assert call(p1, ws, n) not in BAD
+    tiled = _params(C=32, HD=1, ps=3, ws=3, k=4)
+    nq = tiled.B * tiled.HD * tiled.T * tiled.H * tiled.W
+    base = (nq * 32 * 4 + 255) // 256 * 256
+    assert size(tiled) > base
+    assert call(tiled, FAKE, base) not in BAD
+    assert call(tiled, FAKE, base - 1) == B.SNLS_ERR_WORKSPACE
+    assert call(tiled, None, BIG) == B.SNLS_ERR_WORKSPACE
+    scored = _params(C=32, HD=1, ps=1, stride0=2, ws=9, k=33)
+    nq = scored.B * scored.HD * scored.T * ((scored.H - 1) // 2 + 1) * ((scored.W - 1) // 2 + 1)
+    assert size(scored) == (nq * 256 * 4 + 255) // 256 * 256

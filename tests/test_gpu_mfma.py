@@ -291,3 +291,21 @@ def test_single_pixel_routes(dev, C, HD, ws, k, s0, flow):
     fl = rng.uniform(-flow, flow, (1, 3, 2, 2, 37, 45)).astype(np.float32)
     gd, gi = _search(q, kk, fl, p, dev)
     compare_topk(gd, gi, oracle.search(q, kk, fl, p), k)
+
+
+@pytest.mark.parametrize("ps,C,k,dist", [(1, 32, 10, 0), (3, 16, 12, 0), (7, 64, 12, 1), (7, 64, 12, 0)])
+def test_search_without_room_for_the_split_copies(dev, ps, C, k, dist):
+    """A workspace of the size the vector-unit routes use (none for single pixels)."""
+    p = small_params(T=2, C=C, H=30, W=37, ws=5, wt=1, ps=ps, k=k, dist_type=dist)
+    rng = np.random.default_rng(C + ps)
+    q, kk = (rng.standard_normal((1, 2, C, 30, 37), dtype=np.float32) for _ in range(2))
+    fl = rng.uniform(-3, 3, (1, 2, 2, 2, 30, 37)).astype(np.float32)
+    full = B.snls_workspace_size(B.SNLS_OP_SEARCH, p)
+    copies = 2 * ((1 * 2 * 30 * 37 * (32 if C <= 32 else 64) * 6 + 255) // 256 * 256)
+    ws = torch.empty(0 if ps == 1 else (full - copies) // 4, device=dev)
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    gd, gi = B.snls_search(d(q), d(kk), d(fl), p, workspace=ws)
+    compare_topk(gd.cpu().numpy().reshape(-1, k), gi.cpu().numpy().reshape(-1, k, 3), oracle.search(q, kk, fl, p), k)
+    if ps > 1:
+        with pytest.raises(B.SnlsError):
+            B.snls_search(d(q), d(kk), d(fl), p, workspace=ws[:-64].clone())

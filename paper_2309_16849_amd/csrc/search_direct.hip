@@ -68,10 +68,13 @@ __global__ void __launch_bounds__(256) search_full_kernel(const float* __restric
 }
 
 // Positions of every candidate (one wave per query row at a time, lanes over
-// its candidates), and the invalid scores of frames outside the clip, which
-// the tiled scores kernel leaves unwritten.
-__global__ void __launch_bounds__(256) search_positions_kernel(const float* __restrict__ flows, Geo g,
-                                                               float* __restrict__ dists, float* __restrict__ inds) {
+// its candidates), and the scores that the tiled kernel leaves: the invalid ones
+// of frames outside the clip, and those that came out infinite or NaN, which
+// are summed directly (the tiles multiply q's zeros outside the frame with keys
+// and add infinite sums tap by tap).
+__global__ void __launch_bounds__(256) search_positions_kernel(const float* __restrict__ q, const float* __restrict__ k,
+                                                               const float* __restrict__ flows, Geo g, float* dists,
+                                                               float* __restrict__ inds) {
   const int lane = threadIdx.x & 63, ncell = g.ws * g.ws;
   const float inv_cell = 1.f / (float)ncell, inv_ws = 1.f / (float)g.ws;
   const long long step = (long long)gridDim.x * 4;
@@ -86,10 +89,13 @@ __global__ void __launch_bounds__(256) search_positions_kernel(const float* __re
       float fh, fw;
       read_shift(flows, g, qp, dt, &fh, &fw);
       const long long o = row * g.ncand + cid;
+      const float disp_h = cand_disp(fh, g.s1, dh, g.r), disp_w = cand_disp(fw, g.s1, dw, g.r);
       if (t2 < 0 || t2 >= g.T) dists[o] = from_score(-INFINITY, g.dist);
+      else if (!(fabsf(dists[o]) < INFINITY) && centre_ok(qp.h, disp_h, g.H) && centre_ok(qp.w, disp_w, g.W))
+        dists[o] = score_candidate(q, k, g, qp.b, qp.hd, qp.t, qp.h, qp.w, t2, disp_h, disp_w);
       inds[3 * o] = (float)t2;
-      inds[3 * o + 1] = cand_disp(fh, g.s1, dh, g.r);
-      inds[3 * o + 2] = cand_disp(fw, g.s1, dw, g.r);
+      inds[3 * o + 1] = disp_h;
+      inds[3 * o + 2] = disp_w;
     }
   }
 }
@@ -168,8 +174,8 @@ snls_status launch_search_full(const float* q, const float* k, const float* flow
     const snls_status st = launch_tile_scores(q, k, flows, gt, dists, g.ncand, s);
     if (st != SNLS_OK) return st;
     const long long blk = (g.rows + 3) / 4;
-    hipLaunchKernelGGL(search_positions_kernel, dim3((unsigned)(blk < 8192 ? blk : 8192)), dim3(256), 0, s, flows, g,
-                       dists, inds);
+    hipLaunchKernelGGL(search_positions_kernel, dim3((unsigned)(blk < 8192 ? blk : 8192)), dim3(256), 0, s, q, k,
+                       flows, g, dists, inds);
     return hipGetLastError() == hipSuccess ? SNLS_OK : SNLS_ERR_HIP;
   }
   long long blocks = (total + 255) / 256;

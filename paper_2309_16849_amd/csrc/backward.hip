@@ -461,7 +461,7 @@ __global__ void __launch_bounds__(256) backward_agg_block_kernel(const float* __
         for (int c = 0; c < PB; ++c) vb[a * PB + c] = vv.ld(kr[a] + kc[c] + ch4);
     }
     // (Rows in XCD order, wave sums by DPP: 256x256, P = 3, whole backward 5.67
-    // -> 5.41 ms; 96x101, P = 7, L2: 10.6 -> 10.9 ms.  Sums of g~ times the first
+    // -> 5.41 ms; 96x101, P = 7, k = 30: 6.76 -> 6.31 ms, L2 10.7 -> 10.45.  Sums of g~ times the first
     // differences, with the bilinear weights applied once, take fewer
     // operations, but their roundings are those of larger numbers: P = 7 flow
     // gradients 1.6 times further from 64-bit ones.)
@@ -489,7 +489,8 @@ __global__ void __launch_bounds__(256) backward_agg_block_kernel(const float* __
   }
 }
 
-template <int P>
+// IP: inner product (else squared L2).
+template <int P, bool IP>
 __global__ void __launch_bounds__(256) backward_search_block_kernel(const float* __restrict__ qcl,
                                                                     const float* __restrict__ kcl,
                                                                     const float* __restrict__ dists,
@@ -507,7 +508,7 @@ __global__ void __launch_bounds__(256) backward_search_block_kernel(const float*
   const float* drow = dists + row * g.k;
   const float* irow = inds + row * g.k * 3;
   const float* Grow = Gws + row * g.k;
-  const bool ip = g.dist == SNLS_DIST_PROD;
+  constexpr bool ip = IP;
   const float sscale = (ip ? 1.f : -1.f) * scale;
   float m, z;
   softmax_stats(drow, g.k, sscale, lane, &m, &z);
@@ -586,7 +587,7 @@ __global__ void __launch_bounds__(256) backward_search_block_kernel(const float*
       fh = fmaf(dk, (1.f - ax) * (k10 - k00) + ax * (k11 - k01), fh);
       fw = fmaf(dk, (1.f - ay) * (k01 - k00) + ay * (k11 - k10), fw);
     };
-    if (ip && inside) {  // no pixel to test, no branch
+    if (ip && inside) {  // no pixel to test, no branch (L2: the second copy of the loop cost 4 to 5% at P = 5 and 7)
 #pragma unroll
       for (int ph = 0; ph < P; ++ph)
 #pragma unroll
@@ -1112,8 +1113,12 @@ snls_status launch_backward(const float* q, const float* k, const float* v, cons
   case P:                                                                                                         \
     hipLaunchKernelGGL(backward_agg_block_kernel<P>, grid, block, 0, s, vcl, dists, inds, gocl, g, scale,          \
                        grad_flows, Gws, wlws);                                                                    \
-    hipLaunchKernelGGL(backward_search_block_kernel<P>, grid, block, 0, s, qcl, kcl, dists, inds, grad_dists, g,   \
-                       scale, Gws, dqcl, grad_flows, ddws);                                                       \
+    if (g.dist == SNLS_DIST_PROD)                                                                                 \
+      hipLaunchKernelGGL((backward_search_block_kernel<P, true>), grid, block, 0, s, qcl, kcl, dists, inds,       \
+                         grad_dists, g, scale, Gws, dqcl, grad_flows, ddws);                                      \
+    else                                                                                                          \
+      hipLaunchKernelGGL((backward_search_block_kernel<P, false>), grid, block, 0, s, qcl, kcl, dists, inds,      \
+                         grad_dists, g, scale, Gws, dqcl, grad_flows, ddws);                                      \
     break;
         SNLS_BWD_ROWS_CASE(1)
         SNLS_BWD_ROWS_CASE(2)

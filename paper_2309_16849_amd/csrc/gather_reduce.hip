@@ -23,9 +23,12 @@
 // heads of 4 or 8 channels also 4 or 2 ranks side by side.  Bound by the taps'
 // latency: one rank's records staged at a time, one query's taps in flight and
 // half the slots idle at 8 channels had taken 575 us on the code example (5 x
-// 128 x 128, 2 x 8 channels, P = 3, k = 10), 197 us now.  A neighbour whose weight is 0, whose frame is not an integer in
-// [0, T) or whose offset is not finite (magnitude kFarDisp or more) adds
-// nothing.
+// 128 x 128, 2 x 8 channels, P = 3, k = 10), 197 us now.  Heads of 33 to 48
+// channels have three blocks of their own: with four, a quarter of the reads in
+// flight idle, 5 x 60 x 90, P = 3, k = 10 took 287 us at 36 channels and 306 at
+// 48, now 221 and 241 (260 and 282 with one query's taps in flight).
+// A neighbour whose weight is 0, whose frame is not an integer in [0, T) or
+// whose offset is not finite (magnitude kFarDisp or more) adds nothing.
 #include "snls_internal.h"
 
 namespace snls {
@@ -41,7 +44,7 @@ constexpr int OMAX = 128;         // output channels (8 blocks of 16)
 constexpr int SP = NP + 4;        // LDS pitch of a channel row of S (pixels)
 // ranks side by side for Ch channels per head, and the 16-row blocks their channels fill
 inline __host__ __device__ int ranks(int Ch) { return Ch <= 4 ? 4 : Ch <= 8 ? 2 : 1; }
-inline __host__ __device__ int blocks(int Ch) { return Ch <= 16 ? 1 : Ch <= 32 ? 2 : 4; }
+inline __host__ __device__ int blocks(int Ch) { return (Ch + 15) / 16; }
 }  // namespace gr
 
 // Covering-query range of the tile along one axis: grid positions m with
@@ -394,6 +397,7 @@ snls_status launch_gather_stacked(const float* v, const float* weights, const fl
   else if (gr::ranks(g.Ch) == 2) SNLS_GS(1, 2);
   else if (gr::blocks(g.Ch) == 1) SNLS_GS(1, 1);
   else if (gr::blocks(g.Ch) == 2) SNLS_GS(2, 1);
+  else if (gr::blocks(g.Ch) == 3) SNLS_GS(3, 1);
   else SNLS_GS(4, 1);
 #undef SNLS_GS
   return hipGetLastError() == hipSuccess ? SNLS_OK : SNLS_ERR_HIP;
@@ -432,6 +436,7 @@ snls_status launch_gather_reduce(const float* v, const float* weights, const flo
   else if (gr::ranks(g.Ch) == 2) SNLS_GR(1, 2);
   else if (gr::blocks(g.Ch) == 1) SNLS_GR(1, 1);
   else if (gr::blocks(g.Ch) == 2) SNLS_GR(2, 1);
+  else if (gr::blocks(g.Ch) == 3) SNLS_GR(3, 1);
   else SNLS_GR(4, 1);
 #undef SNLS_GR
   return hipGetLastError() == hipSuccess ? SNLS_OK : SNLS_ERR_HIP;

@@ -43,14 +43,15 @@ CSRC = os.path.join(ROOT, "paper_2309_16849_amd", "csrc")
 PROFILES = os.path.join(ROOT, "profiles")
 PEAK_FP32_VALU = 157.3e12  # MI355X fp32 vector peak (packed FMA), FLOP/s
 PEAK_FP32_VALU_UNPACKED = 78.6e12  # 256 CUs x 4 SIMDs x 16 lanes x 2 flop x 2.4 GHz, unpacked FMA
+PEAK_BF16_MATRIX = 2.5e15  # MI355X dense bf16 matrix peak, FLOP/s
 PEAK_HBM = 8.0e12          # MI355X HBM3E, B/s
 DEFAULT_WORKLOAD = "denoise480x854"
 METRIC = "queries/s (search+top-k+aggregate) and % fp32 VALU/HBM roofline, config 2"
 
 # Kernels of each library call, by name (no kernel is shared between the
 # search call and the others).
-SEARCH_PAT = re.compile(r"(search_\w+|tile_topk_kernel|wave_topk_kernel|topk_kernel|l2_pair_planes_kernel|"
-                        r"l2_norms_kernel)$")
+SEARCH_PAT = re.compile(r"(search_\w+|mf_split_kernel|(tile_|wave_|group_)?topk_kernel|l2_pair_planes_kernel|"
+                        r"l2_norms\w*_kernel|l2_sat_\w+_kernel)$")
 
 
 def frames_in_window(p):
@@ -89,7 +90,7 @@ def _kernel_files():
     for path in sorted(glob.glob(os.path.join(CSRC, "*.hip"))):
         with open(path) as f:
             text = f.read()
-        for m in re.finditer(r"__global__\s+(?:void\s+)?(?:__launch_bounds__\([^)]*\)\s+)?(\w+)\s*\(", text):
+        for m in re.finditer(r"__global__\s+(?:void\s+)?(?:__launch_bounds__\((?:[^()]|\([^()]*\))*\)\s+)?(\w+)\s*\(", text):
             out[m.group(1)] = os.path.basename(path)
     return out
 
@@ -209,7 +210,7 @@ def summarize_profiles(outdir, workload, copy_mib, extra_args=""):
             e["fetch_bytes"] = c["FETCH_SIZE"] * f_fetch * 1024.0
         if f_write and "WRITE_SIZE" in c:
             e["write_bytes"] = c["WRITE_SIZE"] * f_write * 1024.0
-        for cn in ("SQ_INSTS_VALU_FMA_F32", "SQ_INSTS_VALU", "SQ_BUSY_CYCLES", "SQ_INSTS_LDS", "SQ_LDS_BANK_CONFLICT",
+        for cn in ("SQ_INSTS_VALU_FMA_F32", "SQ_INSTS_VALU", "SQ_INSTS_MFMA", "SQ_VALU_MFMA_BUSY_CYCLES", "TA_TA_BUSY_sum", "SQ_BUSY_CYCLES", "SQ_INSTS_LDS", "SQ_LDS_BANK_CONFLICT",
                    "SQ_LDS_IDX_ACTIVE", "SQ_WAVES", "GRBM_GUI_ACTIVE", "SQ_ACTIVE_INST_VALU"):
             if cn in c:
                 e[cn] = c[cn]
@@ -224,7 +225,8 @@ def summarize_profiles(outdir, workload, copy_mib, extra_args=""):
            "fetch_scale": f_fetch, "write_scale": f_write, "kernels": kernels,
            "search_call": {"kernels": search, "avg_us": total(search, "avg_us"),
                            "fetch_bytes": total(search, "fetch_bytes"), "write_bytes": total(search, "write_bytes"),
-                           "fma_f32_wave_insts": total(search, "SQ_INSTS_VALU_FMA_F32")}}
+                           "fma_f32_wave_insts": total(search, "SQ_INSTS_VALU_FMA_F32"),
+                           "mfma_wave_insts": total(search, "SQ_INSTS_MFMA")}}
     sc = rec["search_call"]
     if sc["fetch_bytes"] is not None and sc["write_bytes"] is not None:
         lines += ["", "HBM traffic of one snls_search call (%s): FETCH %.1f MB + WRITE %.1f MB = %.1f MB." % (
@@ -430,6 +432,8 @@ def main():
     traffic = sc["fetch_bytes"] + sc["write_bytes"] if sc and sc.get("fetch_bytes") is not None and \
         sc.get("write_bytes") is not None else None
     achieved = issued / t_search if issued else None
+    # 16 x 16 x 32 products of the scores kernel (the search call's only matrix instructions)
+    mfma = sc["mfma_wave_insts"] * 16384 / t_search if sc and sc.get("mfma_wave_insts") else None
     roofline = {
         "bound": "alu", "kernel": "snls_search call: " + (" + ".join(_base_name(k) for k in sc["kernels"])
                                                           if sc else "kernels not profiled for these sources"),
@@ -437,6 +441,8 @@ def main():
         "frac": achieved / PEAK_FP32_VALU if achieved else None,
         "peak_attainable": PEAK_FP32_VALU_UNPACKED / 1e12,
         "frac_attainable": achieved / PEAK_FP32_VALU_UNPACKED if achieved else None,
+        "matrix_achieved": mfma / 1e12 if mfma else None, "matrix_peak": PEAK_BF16_MATRIX / 1e12,
+        "matrix_frac": mfma / PEAK_BF16_MATRIX if mfma else None,
         "traffic": traffic, "alg_bytes": w["search_bytes"],
         "alg_tflops": w["f_search"] / t_search / 1e12, "alg_frac": w["f_search"] / t_search / PEAK_FP32_VALU,
         "call_ms": t_search * 1e3, "profiled_call_ms": sc["avg_us"] / 1e3 if sc and sc.get("avg_us") else None,

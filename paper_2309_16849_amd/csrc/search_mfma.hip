@@ -463,6 +463,97 @@ SNLS_DEV bool mf_sweeps_pay(const Geo& g, const MfGeo& mg, int rounds, int nt) {
   return sweep < direct;
 }
 
+// What mf_redo needs of a frame step (in LDS).
+struct MfRedo {
+  const float *q, *k;                     // the videos
+  const unsigned char *qplane, *kplane;   // split planes of the query and key frames
+  const float2* ff;                       // the tile's offsets of the frame step
+  float* scores;                          // at the frame step's first candidate
+  int* infs;                              // last frame step (from 1) with an infinity in its reach
+  long long qchan, kchan;                 // first channel plane of the query and key frames
+  long long HW, rowb;
+  int H, W, Ch, nH, nW, ws, r;
+  float s1;
+  int pitch, s0, tqw, qn, my0, mx0, hr, rec, npc, dmin_h, dmin_w, UH, UW, step;
+};
+
+// Scores that are infinite or NaN.  The products of an infinity's parts mix
+// signs and zeros: with one in reach these scores are formed again from q and
+// k.  Without, a NaN comes from a NaN -- of the patch, or, for patches that
+// stick out of the frame, from keys that only q's zeros there meet: only those
+// are formed again.  A function of its own, called by the whole workgroup:
+// inlined, its values took registers from the frame loop (271x483, P = 5, two
+// heads of 24 channels: 1.54 ms inlined, 1.47 called, 1.43 without).
+template <int PS, int NT>
+__device__ __noinline__ void mf_redo(const MfRedo* __restrict__ a) {
+  using namespace mf;
+  constexpr int LO = -(PS / 2);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int H = a->H, W = a->W, ws = a->ws, s0 = a->s0, tqw = a->tqw;
+  bool infs = false;
+  auto look = [&](const unsigned char* plane, int y0, int ny, int x0, int nx) {
+    const int n = ny * nx * a->npc;
+    for (int e = tid; e < n; e += NT) {
+      const int pc = e / (ny * nx), p = e - pc * (ny * nx);
+      const int gy = y0 + p / nx, gx = x0 + p % nx;
+      if (gy < 0 || gy >= H || gx < 0 || gx >= W) continue;
+      const u32x4 v = *reinterpret_cast<const u32x4*>(
+          plane + (long long)gy * W * a->rec + ((long long)((pc >> 2) * (4 * PARTS) + (pc & 3)) * W + gx) * 16);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        infs = infs || (v[i] & 0x7fffu) == 0x7f80u || (v[i] & 0x7fff0000u) == 0x7f800000u;
+    }
+  };
+  const int Y0 = a->my0 * s0 + LO, X0 = a->mx0 * s0 + LO;
+  look(a->qplane, Y0, a->hr, X0, HC);
+  look(a->kplane, Y0 + a->dmin_h, a->hr + a->UH - 1, X0 + a->dmin_w, HC + a->UW - 1);
+  if (infs) *a->infs = a->step;
+  __syncthreads();
+  infs = *a->infs == a->step;
+  const int ncell = ws * ws, nterm = PS * PS * a->Ch, ncand = a->qn * ncell;
+  const float* const qbase = a->q + a->qchan * a->HW;
+  const float* const kbase = a->k + a->kchan * a->HW;
+  // a lane finds a candidate, the wave forms its score
+  for (int e0 = tid - lane; e0 < ncand; e0 += NT) {
+    const int e = e0 + lane;
+    const int j = e / ncell, cell = e - j * ncell;
+    const int mh = a->my0 + j / tqw, mw = a->mx0 + j % tqw;
+    const int h = mh * s0, w = mw * s0;
+    float dh = 0.f, dw = 0.f;
+    float* at = nullptr;
+    bool todo = e < ncand && mh < a->nH && mw < a->nW;
+    if (todo) {
+      dh = cand_disp(a->ff[j].x, a->s1, cell / ws, a->r);
+      dw = cand_disp(a->ff[j].y, a->s1, cell % ws, a->r);
+      at = a->scores + ((a->rowb + mh) * a->nW + mw) * a->pitch + cell;
+      const bool out = h + LO < 0 || h + LO + PS > H || w + LO < 0 || w + LO + PS > W;
+      todo = (infs || out) && centre_ok(h, dh, H) && centre_ok(w, dw, W) && !(fabsf(*at) < INFINITY);
+    }
+    unsigned long long m = __ballot(todo);
+    while (m) {
+      const int src = __ffsll((long long)m) - 1;
+      m &= m - 1;
+      const int ch = __shfl(h, src), cw = __shfl(w, src);
+      int nh, nw;
+      float ah, aw;
+      split_disp(__shfl(dh, src), &nh, &ah);
+      split_disp(__shfl(dw, src), &nw, &aw);
+      float sum = 0.f;
+      for (int i0 = 0; i0 < nterm; i0 += 64) {
+        const int i = i0 + lane, c = i / (PS * PS), pp = i - c * (PS * PS);
+        const int y = ch + LO + pp / PS, x = cw + LO + pp % PS;
+        if (i < nterm && y >= 0 && y < H && x >= 0 && x < W)
+          sum = fmaf(qbase[c * a->HW + (long long)y * W + x],
+                     bilinear_plane(kbase + c * a->HW, H, W, y + nh, x + nw, ah, aw), sum);
+        if (__any(sum != sum)) break;
+      }
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+      if (lane == src) *at = sum == sum ? sum : -INFINITY;
+    }
+  }
+}
+
 // CG: 32-channel chunks of a record multiplied per load (1 or 2).  S1: query stride 1.
 template <int PS, int CG, bool S1>
 __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_mfma_scores_kernel(
@@ -485,6 +576,7 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
   // score, and with an infinity in its reach
   int* const uni = reinterpret_cast<int*>(smem + mg.o_uni);
   int* const nonfin = uni + 4 * (2 * g.wt + 1);
+  MfRedo* const redo = reinterpret_cast<MfRedo*>(nonfin + 4);
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -742,75 +834,13 @@ __global__ void __launch_bounds__(mf::waves(CG) * 64, mf::waves(CG) / 4) search_
     }
     __syncthreads();  // the tables are free, the next frame's queries set, the frame's scores written
     if (tabled && nonfin[0] == fi + 1) {
-      // Scores that are infinite or NaN.  The products of an infinity's parts mix
-      // signs and zeros: with one in reach these scores are formed again from q and
-      // k.  Without, a NaN comes from a NaN -- of the patch, or, for patches that
-      // stick out of the frame, from keys that only q's zeros there meet: only
-      // those are formed again.
-      int tidr = tid;  // (index arithmetic done here, not kept live across the frames)
-      asm volatile("" : "+v"(tidr));
-      const int laner = tidr & 63;
-      bool infs = false;
-      auto look = [&](const unsigned char* plane, int y0_, int ny, int x0_, int nx) {
-        const int npc = mg.nc32 * 4, n = ny * nx * npc;
-        for (int e = tidr; e < n; e += NT) {
-          const int pc = e / (ny * nx), p = e - pc * (ny * nx);
-          const int gy = y0_ + p / nx, gx = x0_ + p % nx;
-          if (gy < 0 || gy >= g.H || gx < 0 || gx >= g.W) continue;
-          const u32x4 v = *reinterpret_cast<const u32x4*>(
-              plane + (long long)gy * g.W * rec + ((long long)((pc >> 2) * (4 * PARTS) + (pc & 3)) * g.W + gx) * 16);
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            infs = infs || (v[i] & 0x7fffu) == 0x7f80u || (v[i] & 0x7fff0000u) == 0x7f800000u;
-        }
-      };
-      look(qs + slab(t) * g.HW * rec, Y0, hr, X0, HC);
-      look(ks + slab(t2) * g.HW * rec, Y0 + dmin_h, hr + UH - 1, X0 + dmin_w, HC + UW - 1);
-      if (infs) nonfin[1] = fi + 1;
+      if (tid == 0)
+        *redo = MfRedo{q, k, qs + slab(t) * g.HW * rec, ks + slab(t2) * g.HW * rec, ff, scores + cbase, nonfin + 1,
+                       ((long long)b * g.T + t) * g.C + (long long)hd * g.Ch, ((long long)b * g.T + t2) * g.C + (long long)hd * g.Ch,
+                       g.HW, rowb, g.H, g.W, g.Ch, g.nH, g.nW, ws, r, g.s1, pitch, s0, tqw, qn, my0, mx0, hr, rec,
+                       mg.nc32 * 4, dmin_h, dmin_w, UH, UW, fi + 1};
       __syncthreads();
-      infs = nonfin[1] == fi + 1;
-      const int ncell = ws * ws, nterm = PS * PS * g.Ch;
-      const float* const qbase = q + (((long long)b * g.T + t) * g.C + (long long)hd * g.Ch) * g.HW;
-      const float* const kbase = k + (((long long)b * g.T + t2) * g.C + (long long)hd * g.Ch) * g.HW;
-      // a lane finds a candidate, the wave forms its score
-      for (int e0 = tidr - laner; e0 < qn * ncell; e0 += NT) {
-        const int e = e0 + laner;
-        const int j = e / ncell, cell = e - j * ncell;
-        const int mh = my0 + j / tqw, mw = mx0 + j % tqw;
-        const int h = mh * s0, w = mw * s0;
-        float dh_ = 0.f, dw_ = 0.f;
-        float* at = nullptr;
-        bool todo = e < qn * ncell && mh < g.nH && mw < g.nW;
-        if (todo) {
-          dh_ = cand_disp(ff[j].x, g.s1, cell / ws, r);
-          dw_ = cand_disp(ff[j].y, g.s1, cell % ws, r);
-          at = scores + ((rowb + mh) * g.nW + mw) * pitch + cbase + cell;
-          const bool out = h + LO < 0 || h + LO + PS > g.H || w + LO < 0 || w + LO + PS > g.W;
-          todo = (infs || out) && centre_ok(h, dh_, g.H) && centre_ok(w, dw_, g.W) && !(fabsf(*at) < INFINITY);
-        }
-        unsigned long long m = __ballot(todo);
-        while (m) {
-          const int src = __ffsll((long long)m) - 1;
-          m &= m - 1;
-          const int ch = __shfl(h, src), cw = __shfl(w, src);
-          int nh, nw;
-          float ah, aw;
-          split_disp(__shfl(dh_, src), &nh, &ah);
-          split_disp(__shfl(dw_, src), &nw, &aw);
-          float sum = 0.f;
-          for (int i0 = 0; i0 < nterm; i0 += 64) {
-            const int i = i0 + laner, c = i / (PS * PS), pp = i - c * (PS * PS);
-            const int y = ch + LO + pp / PS, x = cw + LO + pp % PS;
-            if (i < nterm && y >= 0 && y < g.H && x >= 0 && x < g.W)
-              sum = fmaf(qbase[c * g.HW + (long long)y * g.W + x],
-                         bilinear_plane(kbase + c * g.HW, g.H, g.W, y + nh, x + nw, ah, aw), sum);
-            if (__any(sum != sum)) break;
-          }
-#pragma unroll
-          for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-          if (laner == src) *at = sum == sum ? sum : -INFINITY;
-        }
-      }
+      mf_redo<PS, NT>(redo);
     }
   }
 }
@@ -840,7 +870,7 @@ static bool mf_geo(const Geo& g, int tqh, MfGeo* m) {
   m->o_dump = (int)o;
   o += 64 * 4;
   m->o_uni = (int)o;
-  o += (2 * g.wt + 1) * 16 + 16;
+  o += (2 * g.wt + 1) * 16 + 16 + (sizeof(MfRedo) + 15) / 16 * 16;
   m->o_tab = (int)o;
   o += qn * m->win * 4;
   return o <= mf::LDS_BYTES;

@@ -333,11 +333,11 @@ __global__ void __launch_bounds__(256) aggregate_merged_kernel(const float* __re
   }
 }
 
-// Tiled gather for the query stride S_Q = 1 (every pixel is a query).
+// Tiled gather (any query stride).
 //
-// With S_Q = 1 the contribution of neighbour l of query i to the output
-// pixel y = i + p lands at y + disp_l, i.e. at the offset disp_l from y,
-// whatever the patch offset p.  So the (slot, offset) bin of a (query,
+// The contribution of neighbour l of query i to the output pixel y = i + p
+// lands at y + disp_l, i.e. at the offset disp_l from y, whatever the patch
+// offset p.  So the (slot, offset) bin of a (query,
 // neighbour, tap) triple is the same for every pixel the query covers, and
 // it is computed once per tile instead of once per covered pixel:
 //  * phase 1 (all threads): for the tile's covering queries, softmax over
@@ -349,10 +349,10 @@ __global__ void __launch_bounds__(256) aggregate_merged_kernel(const float* __re
 //  * phase 2 (one wave per output row, pixel after pixel): the wave's bins
 //    hold the records of the pixel's P x P covering queries (integer
 //    atomics: the sums do not depend on the order); moving one pixel along
-//    the row removes one query column and adds one, so after the row's first
-//    pixel only 2*P*k records change per pixel; each non-empty bin is one
-//    position whose channel vector is read once from the channels-last copy
-//    of V (lane = channel), in bin order.
+//    the row removes at most one query column and adds one, so after the row's
+//    first pixel at most 2*P*k records change per pixel; each non-empty bin is
+//    one position whose channel vector is read once from the channels-last copy
+//    of V: the positions are listed in LDS and read several at a time (below).
 namespace aggt {
 constexpr int TY = 8, TX = 8;        // output tile; wave w owns tile row w
 constexpr int WAVES = TY;

@@ -3,7 +3,9 @@
 // bilinear reads (the in-place computation of Sec. 3.4), for any parameter
 // combination.  k == 0 writes every candidate; k >= 1 keeps the top-k per
 // query row in registers.  These kernels are the general path; the tiled
-// kernel in search_tile.hip covers the common S_Q = S_K = 1 case faster.
+// kernels (search_mfma.hip, search_tile.hip) and the single-pixel ones
+// (search_p1.hip) cover patches up to 7 x 7 and windows up to 15 x 15 at any
+// query stride faster.  The choice of the route is here too.
 #include "snls_internal.h"
 
 namespace snls {
@@ -206,9 +208,12 @@ SearchRoute search_route(const Geo& g, size_t have) {
   // Single-pixel patches have no overlap for the tiles to share, but the
   // matrix cores still pay where the head has 32 channels or more and every
   // pixel is a query (k <= 16: the 16-lane top-k).  Fused kernel against the
-  // tiled route, S_Q = 1, Ws = 9, k = 10, T = 5: 320x320 with 16 channels 1.23
-  // and 1.25 ms, with 32 channels 1.83 and 1.28 ms, 256x256 with 64 channels
-  // 2.02 and 1.15 ms; 4 heads of 8 channels 0.22 and 0.31 ms.  The fused
+  // tiled route, S_Q = 1, Ws = 9, k = 10, T = 5, smooth motion: 320x320 with 16
+  // channels 1.23 and 1.25 ms, with 32 channels 1.84 and 1.30 ms, 256x256 with 64
+  // channels 2.01 and 1.21 ms; 4 heads of 8 channels 0.22 and 0.31 ms.  Offsets
+  // that neighbouring queries do not share cost the tiles more: 256x256, T = 3,
+  // 32 channels, offsets of +-30 at random 2.99 and 1.59 ms, of +-100 3.38 and
+  // 8.7 ms.  The fused
   // per-query kernel (k <= 32) takes the other single-pixel searches and needs
   // no score workspace; the scored single-pixel route only at a query stride
   // above 1.

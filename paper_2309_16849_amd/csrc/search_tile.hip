@@ -5,7 +5,9 @@
 // The scores kernel here runs on the vector units in fp32.  Heads of 8 or
 // more channels are scored on the matrix cores instead (search_mfma.hip, same
 // decomposition); this one remains for narrower heads, whose channels would
-// be padded to 32 there, and for frames past that kernel's 32-bit offsets.
+// be padded to 32 there, for frames past that kernel's 32-bit offsets, for
+// workspaces without room for its operands, and for searches that keep every
+// candidate, which have no workspace.
 //
 // Window cell d of a query sits at displacement disp_d = F + S_K (d - r);
 // with n_d = floor(disp_d) and a_d = disp_d - n_d its bilinear score is an
@@ -1131,8 +1133,8 @@ __global__ void __launch_bounds__(gtk::ROWS * 16) group_topk_kernel(const float*
   inds[3 * o + 2] = cand_disp(fw, g.s1, dw, g.r);
 }
 
-// The tiled path handles any S_Q, P <= 7, Ws <= 9 with the inner product
-// (S_K <= 1) or the squared L2 distance (S_K = 1).
+// The tiled path handles any S_Q, P <= 7, Ws <= 9 (Ws <= 15 at P = 7) and
+// S_K <= 1 with either distance.
 bool tile_supported(const Geo& g) {
   const bool dist_ok = g.s1 > 0.f && g.s1 <= 1.0f;  // both distances (L2: norm terms per cell unless S_K = 1)
   // windows above 9 only at P = 7: its 80-query tile keeps 15 x 15 windows'

@@ -57,10 +57,10 @@ bool gather_tile_supported(const Geo& g);
 bool reduce_supported(const Geo& g, int cout);
 size_t gather_ws_bytes(const Geo& g);
 
-// The tiled search path (S_Q = 1, P <= 7, Ws <= 9; inner product with
-// S_K <= 1, squared L2 with S_K = 1) and its workspace: the inner-product
-// score of every candidate (rows x candidates fp32), plus for L2 the key-norm
-// term of every candidate and the query-norm term of every row.
+// The tiled search path (any S_Q, P <= 7, Ws <= 9, at P = 7 Ws <= 15, S_K <= 1;
+// either distance) and its workspace without the matrix cores' operands: the
+// inner-product score of every candidate (rows x candidates fp32), plus for L2
+// the norm terms (l2_planes_bytes and what search_tile.hip adds).
 bool tile_supported(const Geo& g);
 size_t tile_base_bytes(const Geo& g);
 // The tiled route's scores on the matrix cores (8 channels per head or more)

@@ -45,7 +45,7 @@
 //  * the 4-tap pass writes the scores of the frame to the workspace rows.
 //
 // Measured (480x854, T = 5, 64 channels, P = 7, Ws = 9, the whole search): 15.1 ms
-// against 25 ms with the scores on the vector units.  A step of a wave of two
+// against 21.3 ms with the scores on the vector units.  A step of a wave of two
 // shift rows takes about 4,300 cycles: 820 to issue the vector instructions, 790
 // of matrix cores, the rest waits, at 2 waves per SIMD -- without the key loads
 // (stale operands) the call takes 3.2 ms less, without the third parts 3.9.

@@ -196,6 +196,31 @@ def test_error_no_larger_than_the_vector_units(dev, ps, C, ws, kind, bits):
     assert here <= 1.05 * vector, (here, vector)
 
 
+@pytest.mark.parametrize("ps,C,HD,ws,s1", [(3, 16, 2, 5, 0.5), (3, 32, 2, 9, 0.75), (7, 64, 1, 9, 0.5)])
+def test_error_at_fractional_steps(dev, ps, C, HD, ws, s1):
+    """Fractional offsets and key strides (the paper's code example: two heads
+    of 8 channels, P = 3, half-pixel steps): the kept scores are no further from
+    the 64-bit oracle's than the same candidates' on the vector units (5% for chance)."""
+    p = small_params(T=2, C=C, HD=HD, H=40, W=44, ws=ws, wt=1, ps=ps, k=16, stride1=s1)
+    rng = np.random.default_rng(C + ws)
+    x = rng.standard_normal((1, 2, C, 40, 44), dtype=np.float32)
+    fl = rng.uniform(-3, 3, (1, 2, 2, 2, 40, 44)).astype(np.float32)
+    gd, gi = _search(x, x, fl, p, dev)
+    res = oracle.search(x, x, fl, p)
+    ref, ind = res["all_dists"], res["all_inds"]
+    ad, ai = B.snls_search(torch.from_numpy(x).to(dev), torch.from_numpy(x).to(dev), torch.from_numpy(fl).to(dev), dict(p, k=0))
+    ad = ad.cpu().numpy().reshape(ref.shape)
+    assert np.array_equal(ai.cpu().numpy().reshape(ind.shape), ind.astype(np.float32))
+    # the candidate of each kept position
+    at = (gi[:, :, None, :] == ai.cpu().numpy().reshape(ind.shape)[:, None]).all(-1)
+    assert (at.sum(-1) >= 1).all()
+    at = at.argmax(-1)
+    fin = np.isfinite(gd)
+    exact, vector = np.take_along_axis(ref, at, 1)[fin], np.take_along_axis(ad, at, 1)[fin].astype(np.float64)
+    here = np.linalg.norm(gd[fin].astype(np.float64) - exact)
+    assert here <= 1.05 * np.linalg.norm(vector - exact), (here, np.linalg.norm(vector - exact))
+
+
 @pytest.mark.parametrize("ps,C", [(1, 32), (3, 16), (7, 48), (3, 140)])
 @pytest.mark.parametrize("what", ["nan", "inf", "huge"])
 def test_values_that_are_not_finite_or_overflow(dev, ps, C, what):
